@@ -2,6 +2,7 @@
 // and the odd-even pieces of the coarsest solve.
 #include "coarse.h"
 #include "coarse_dev.h"
+#include "fine_dev.h"
 
 #include <algorithm>
 
@@ -246,84 +247,177 @@ __global__ void __launch_bounds__(64 * SW) k_capply(CoarseOpView<T, S> op, const
 }
 
 // ---------------------------------------------------------------------------
-// Batched apply on the matrix cores (FP32 arithmetic, 8..16 right-hand
-// sides per launch chunk).  Per site the product is a complex GEMM
-//   out (d x nb) = [K_0 .. K_8] (d x 9d)  *  [in(nbr_0); ..; in(nbr_8)] (9d x nb),
-// done as real 16x16x4 MFMA tiles: rows i of a 16-row tile, RHS r in the
-// 16 columns, four complex GEMM columns per step and four real products per
-// step (Cr += Ar Br - Ai Bi, Ci += Ar Bi + Ai Br).  Wavefront w handles row
-// tile w / 3 against block group w % 3 (blocks 3g .. 3g+2); the three
-// partial tiles are summed through LDS.  The B operand (the nine input
-// vectors of the site for every RHS, [9d][16] complex) is staged in LDS.
+// Batches on the matrix cores (FP32 arithmetic, up to 16 right-hand sides per
+// launch chunk).  Per site the product is a complex GEMM
+//   out (d x nr) = [K_k, k in mask] (d x ns d)  *  [in(nbr_k); ..] (ns d x nr),
+// done as real 16x16x4 MFMA tiles: rows i of a 16-row tile, right-hand side r
+// in the 16 columns, four complex GEMM columns per step and four real
+// products per step (Cr += Ar Br - Ai Bi, Ci += Ar Bi + Ai Br).  A workgroup
+// is one site with one wavefront per row tile, so a wavefront holds its rows
+// of the result complete in registers and the epilogue works on them there.
+// The A operand goes from memory straight to registers, several blocks in
+// flight before the workgroup waits for its input vectors; the B operand
+// (the input vectors of every right-hand side) is staged in LDS with
+// contiguous reads along a site's components, the pitch odd so that neither
+// the staging writes (components along the lanes) nor the operand reads
+// (right-hand sides along the lanes) meet on a bank.
 // Operand layout of v_mfma_f32_16x16x4f32: lane l supplies A[l % 16][l / 16]
 // and B[l / 16][l % 16]; result register v of lane l is D[4 (l / 16) + v][l % 16].
 // ---------------------------------------------------------------------------
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 constexpr int MFMA_NB = 16;        // right-hand sides per launch chunk
-constexpr int MFMA_MAXD = 56;      // B tile [9d][16] complex within 64 KiB of LDS
+constexpr int MFMA_LDS = 64512;    // dynamic LDS of a workgroup (B tile)
 
+// the s-th set bit of a block mask, -1 past the last
+__device__ inline int mask_slot(unsigned mask, int s) {
+  for (; s > 0; --s) mask &= mask - 1u;
+  return mask ? __builtin_ctz(mask) : -1;
+}
+// the index of this wavefront in its workgroup, in a scalar register
+__device__ inline int wave_id() { return __builtin_amdgcn_readfirstlane(threadIdx.x >> 6); }
+
+// One wavefront's 16 rows of the operator blocks of a site: a ring of DEP
+// blocks in registers, the next block loaded where one has been applied
 template <typename S, int NJ>
-__global__ void __launch_bounds__(64 * 12) k_capply_mfma(CoarseOpView<float, S> op, const float2* __restrict__ in,
-                                                         float2* __restrict__ out, long long n, int nb) {
-  extern __shared__ float2 lds_b[];   // [9d][16] B tile; reused for the partial tiles
-  const int site = blockIdx.x, d = op.d;
-  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
-  const int nmt = (d + 15) >> 4;
-  in += (long long)blockIdx.y * MFMA_NB * n;
-  out += (long long)blockIdx.y * MFMA_NB * n;
-  const int nr = min(MFMA_NB, nb - (int)blockIdx.y * MFMA_NB);
-  for (int e = threadIdx.x; e < 9 * d * MFMA_NB; e += blockDim.x) {
-    const int j = e / MFMA_NB, r = e % MFMA_NB, k = j / d, jj = j % d;
-    lds_b[e] = r < nr ? in[r * n + (size_t)op.nbr9[site * 9 + k] * d + jj] : make_float2(0.f, 0.f);
+struct MfmaRows {
+  // deeper rings (5 and 3) cost a wavefront per SIMD and measured 7 % slower
+  static constexpr int DEP = sizeof(S) == 4 ? 3 : 2;
+  S a[DEP][NJ];
+  const S* Kx;
+  unsigned mask;
+  int ns, d, lo, kk;
+  __device__ __forceinline__ void load(int u, int s) {
+    const S* Kb = Kx + (unsigned)(mask_slot(mask, s) * d * d);
+#pragma unroll
+    for (int t = 0; t < NJ; ++t) {
+      // columns past d repeat column d - 1 (they meet zero rows of B)
+      const unsigned o = (t + 1) * 4 <= d ? (unsigned)(lo + (4 * t + kk) * d) : (unsigned)(lo + min(4 * t + kk, d - 1) * d);
+      a[u][t] = Kb[o];
+    }
   }
-  __syncthreads();
-  f32x4 cr = {0.f, 0.f, 0.f, 0.f}, ci = {0.f, 0.f, 0.f, 0.f};
-  const int mt = w / 3, g = w % 3;
-  if (mt < nmt) {
-    const int i = mt * 16 + (lane & 15);
-    const bool iv = i < d;
-    const int ic = iv ? i : 0;
-    const int kk = lane >> 4, rl = lane & 15;
-    const size_t bsz = (size_t)d * d;
+  __device__ __forceinline__ void prefetch(const S* __restrict__ Kx_, unsigned mask_, int row, int kk_, int d_) {
+    Kx = Kx_;
+    mask = mask_;
+    ns = __builtin_popcount(mask_);
+    d = d_;
+    lo = row;
+    kk = kk_;
+#pragma unroll
+    for (int u = 0; u < DEP; ++u)
+      if (u < ns) load(u, u);
+  }
+  // lds_b: [ns][4 NJ][pitch], this lane's column rl
+  __device__ __forceinline__ void apply(const float2* lds_b, int pitch, int rl, f32x4& cr, f32x4& ci) {
+    cr = {0.f, 0.f, 0.f, 0.f};
+    ci = {0.f, 0.f, 0.f, 0.f};
+    const float2* bt = lds_b + kk * pitch + rl;
 #pragma unroll 1
-    for (int k = 3 * g; k < 3 * g + 3; ++k) {
-      const S* Kb = op.K + ((size_t)site * 9 + k) * bsz + ic;
-      S a[NJ];
+    for (int s0 = 0; s0 < ns; s0 += DEP) {
 #pragma unroll
-      for (int t = 0; t < NJ; ++t) a[t] = Kb[(size_t)(4 * t + kk) * d];
-      const float2* bt = lds_b + (size_t)(k * d + kk) * MFMA_NB + rl;
+      for (int u = 0; u < DEP; ++u)
+        if (s0 + u < ns) {
 #pragma unroll
-      for (int t = 0; t < NJ; ++t) {
-        float2 av = ldc<float, S>(a[t]);
-        if (!iv) av = make_float2(0.f, 0.f);
-        const float2 bv = bt[(size_t)4 * t * MFMA_NB];
-        cr = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, cr, 0, 0, 0);
-        cr = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.y, cr, 0, 0, 0);
-        ci = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.y, ci, 0, 0, 0);
-        ci = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.x, ci, 0, 0, 0);
+          for (int t = 0; t < NJ; ++t) {
+            const float2 av = ldc<float, S>(a[u][t]);
+            const float2 bv = bt[((s0 + u) * 4 * NJ + 4 * t) * pitch];
+            cr = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.y, ci, 0, 0, 0);
+            cr = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.y, cr, 0, 0, 0);
+            ci = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.x, ci, 0, 0, 0);
+          }
+          if (s0 + u + DEP < ns) load(u, s0 + u + DEP);
+        }
+    }
+  }
+};
+
+// Stages the input vectors of a site: row (k, r), slot k of the mask and
+// right-hand side r, is one wavefront's contiguous read, U of them in flight
+// at a time; get(r, o) loads element o of right-hand side r, fin(r, v) turns
+// what was loaded into the staged value, and mid() runs once after the first
+// loads are issued.  The neighbour of slot k is read once into lane k and
+// broadcast from there, so that no row waits on an index.  Rows past d of a
+// slot are zeroed (they meet the repeated operator columns).
+template <int NJ, typename G, typename F, typename M>
+__device__ __forceinline__ void mfma_stage(float2* lds_b, int pitch, unsigned mask, const int* __restrict__ nb9, int w,
+                                           int nw, int lane, int d, int nr, G&& get, F&& fin, M&& mid) {
+  constexpr int U = 8;
+  const int ns = __builtin_popcount(mask), np = ns * nr, lc = min(lane, d - 1);
+  int nbr = 0;
+  if (lane < ns) nbr = nb9[mask_slot(mask, lane)];
+  const int dr = nw / ns, dk = nw - dr * ns;
+  int r = w / ns, k = w - r * ns;
+  if (w >= np) mid();   // a wavefront without a row still meets mid()'s barrier
+  for (int p0 = w; p0 < np; p0 += U * nw) {
+    decltype(get(0, 0u)) v[U];
+    int r1 = r, k1 = k;
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int rc = min(r1, nr - 1);
+      v[u] = get(rc, (unsigned)(__builtin_amdgcn_readlane(nbr, k1) * d + lc));
+      r1 += dr;
+      k1 += dk;
+      if (k1 >= ns) k1 -= ns, ++r1;
+    }
+    if (p0 == w) mid();
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      if (r < nr && lane < 4 * NJ) {
+        const float2 f = fin(r, v[u]);
+        lds_b[(k * 4 * NJ + lane) * pitch + r] = lane < d ? f : make_float2(0.f, 0.f);
       }
+      r += dr;
+      k += dk;
+      if (k >= ns) k -= ns, ++r;
     }
   }
-  __syncthreads();   // B tile no longer needed: reuse LDS for the partials
-  float2* part = lds_b;   // [3][nmt][16 rows][16 rhs]
-  if (mt < nmt) {
+}
+
+// Rows 4 (l / 16) .. + 3 of the tile and right-hand side l % 16 belong to
+// lane l: calls f(v, o) for each row that exists, o its offset in the field
+template <typename F>
+__device__ __forceinline__ void mfma_rows(int mt, int lane, int d, F&& f) {
 #pragma unroll
-    for (int v = 0; v < 4; ++v) {
-      const int row = 4 * (lane >> 4) + v;
-      part[((size_t)(g * nmt + mt) * 16 + row) * 16 + (lane & 15)] = make_float2(cr[v], ci[v]);
-    }
+  for (int v = 0; v < 4; ++v) {
+    const int i = mt * 16 + 4 * (lane >> 4) + v;
+    if (i < d) f(v, i);
   }
+}
+
+// out = K in over the sites of `sites` (nullptr: every site), or with b
+// given out = b - K in (the residual of a SAP colour pass)
+template <typename S, int NJ>
+__global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_capply_mfma(CoarseOpView<float, S> op, const int* __restrict__ sites,
+                                                               const float2* __restrict__ in,
+                                                               const float2* __restrict__ b, float2* __restrict__ out,
+                                                               long long n, int nb, int per) {
+  extern __shared__ float2 lds_b[];
+  const int wg = xcd_slab_index(blockIdx.x, gridDim.x);
+  const int site = sites ? sites[wg] : wg, d = op.d;
+  const int w = wave_id(), lane = threadIdx.x & 63;
+  constexpr int nmt = (NJ + 3) / 4;
+  const long long off = (long long)blockIdx.y * per * n;
+  in += off;
+  out += off;
+  const int nr = min(per, nb - (int)blockIdx.y * per), pitch = nr | 1;
+  const int kk = lane >> 4, rl = min(lane & 15, nr - 1);
+  MfmaRows<S, NJ> mr;
+  mr.prefetch(op.K + (size_t)site * 9 * d * d, 0x1FFu, min(w * 16 + (lane & 15), d - 1), kk, d);
+  mfma_stage<NJ>(
+      lds_b, pitch, 0x1FFu, op.nbr9 + (size_t)site * 9, w, nmt, lane, d, nr,
+      [&](int r, unsigned o) { return in[r * n + o]; }, [](int, float2 v) { return v; }, [] {});
+  const long long own = (long long)site * d + rl * n;
+  float2 bv[4];
+  if (b) mfma_rows(w, lane, d, [&](int v, int i) { bv[v] = b[off + own + i]; });
   __syncthreads();
-  for (int e = threadIdx.x; e < nmt * 16 * 16; e += blockDim.x) {
-    const int mtile = e / 256, row = (e / 16) % 16, r = e % 16;
-    const int i = mtile * 16 + row;
-    if (i < d && r < nr) {
-      float2 sum = part[((size_t)(0 * nmt + mtile) * 16 + row) * 16 + r];
-      sum = cadd(sum, part[((size_t)(1 * nmt + mtile) * 16 + row) * 16 + r]);
-      sum = cadd(sum, part[((size_t)(2 * nmt + mtile) * 16 + row) * 16 + r]);
-      out[r * n + (size_t)site * d + i] = sum;
-    }
-  }
+  f32x4 cr, ci;
+  mr.apply(lds_b, pitch, rl, cr, ci);
+  if ((lane & 15) < nr)
+    mfma_rows(w, lane, d, [&](int v, int i) {
+      float2 o = make_float2(cr[v], ci[v]);
+      if (b) o = csub(bv[v], o);
+      out[own + i] = o;
+    });
 }
 
 template <int LO, int HI, typename F>
@@ -336,17 +430,45 @@ inline void with_int(int v, F&& f) {
   }
 }
 
-// whether the matrix-core path takes a batch of nb on d components
-inline bool use_mfma(int d, int nb) { return nb >= 8 && d % 4 == 0 && d <= MFMA_MAXD; }
+// The launch of a batch of nb fields on d components with ns staged blocks:
+// chunks of `per` right-hand sides (equal chunks of at most 16, fewer where
+// the B tile would pass 63 KiB) and their LDS bytes
+struct MfmaShape {
+  int per, nch, nmt, nj;
+  size_t lds;
+};
+inline MfmaShape mfma_shape(int d, int nb, int ns) {
+  MfmaShape m;
+  m.nj = (d + 3) / 4;
+  m.nmt = (m.nj + 3) / 4;
+  const int row = ns * 4 * m.nj * (int)sizeof(float2);
+  int cap = std::min(MFMA_NB, MFMA_LDS / row);
+  if ((cap | 1) * row > MFMA_LDS) --cap;       // the pitch is odd
+  m.nch = (nb + cap - 1) / cap;
+  m.per = (nb + m.nch - 1) / m.nch;
+  m.lds = (size_t)(m.per | 1) * row;
+  return m;
+}
+
+// Whether the matrix cores take a batch of nb in FP32 arithmetic.  The
+// matrix-core kernels read the operator once for up to 16 fields but spend 16
+// columns of products on any batch; the vector kernels read it once per
+// four fields (then per two, then per one).  Measured on 8^3x16 sites, d = 40,
+// FP16 storage, operator apply in us (vector / matrix cores): nb = 2 103 /
+// 186, 3 190 / 189, 4 150 / 190, 5 235 / 193, 8 297 / 203, 16 312 / 304; five
+// SAP sweeps in ms: nb = 2 2.42 / 3.06, 3 3.96 / 3.15, 4 3.25 / 3.20, 5 4.81 /
+// 3.33, 8 6.14 / 3.54, 12 9.03 / 4.10, 20 14.9 / 7.2.  So only the batches of
+// two and four, which the vector kernels take in one launch, stay with them.
+inline bool use_mfma(int nb) { return nb == 3 || nb >= 5; }
 
 template <typename S>
-void coarse_apply_mfma(const CoarseOpView<float, S>& op, const float2* in, float2* out, hipStream_t s, int nb) {
+void coarse_apply_mfma(const CoarseOpView<float, S>& op, const int* sites, int nsites, const float2* in,
+                       const float2* b, float2* out, hipStream_t s, int nb) {
   const long long n = (long long)op.V * op.d;
-  const int nmt = (op.d + 15) / 16;
-  const size_t lds = std::max((size_t)9 * op.d * MFMA_NB, (size_t)3 * nmt * 256) * sizeof(float2);
-  const int nch = (nb + MFMA_NB - 1) / MFMA_NB;
-  with_int<1, MFMA_MAXD / 4>(op.d / 4, [&](auto nj) {
-    k_capply_mfma<S, decltype(nj)::value><<<dim3(op.V, nch), 64 * 3 * nmt, lds, s>>>(op, in, out, n, nb);
+  const MfmaShape m = mfma_shape(op.d, nb, 9);
+  with_int<1, 16>(m.nj, [&](auto nj) {
+    k_capply_mfma<S, decltype(nj)::value><<<dim3(nsites, m.nch), 64 * m.nmt, m.lds, s>>>(
+        op, sites, in, b, out, n, nb, m.per);
   });
   DD_LAUNCH_CHECK();
 }
@@ -354,8 +476,8 @@ void coarse_apply_mfma(const CoarseOpView<float, S>& op, const float2* in, float
 template <typename T, typename S>
 void coarse_apply(const CoarseOpView<T, S>& op, const C<T>* in, C<T>* out, hipStream_t s, int nb) {
   if constexpr (std::is_same<T, float>::value) {
-    if (use_mfma(op.d, nb)) {
-      coarse_apply_mfma<S>(op, in, out, s, nb);
+    if (use_mfma(nb) && op.d <= 64) {
+      coarse_apply_mfma<S>(op, nullptr, op.V, in, nullptr, out, s, nb);
       return;
     }
   }
@@ -694,6 +816,132 @@ inline bool use_sap_q1(const SapTables& tb, int d) {
   }
 }
 
+// sums over each group of 16 lanes of the step-size sums of field r0 + lane /
+// 16 in one block (block-major per-site partials): every lane of the group
+// gets the step size
+__device__ inline float2 block_alpha_row(const float* __restrict__ part, int blk, int bs, int lane) {
+  float s0 = 0.f, s1 = 0.f, s2 = 0.f;
+  for (int v = lane & 15; v < bs; v += 16) {
+    const float* p = part + ((size_t)blk * bs + v) * 4;
+    s0 += p[0];
+    s1 += p[1];
+    s2 += p[2];
+  }
+  s0 = row_sum16(s0);
+  s1 = row_sum16(s1);
+  s2 = row_sum16(s2);
+  return s2 > 0.f ? make_float2(s0 / s2, s1 / s2) : czero<float>();
+}
+
+// The MR step of a batch on the matrix cores (the product as in
+// k_capply_mfma, over the in-block operator blocks of a site).  Workgroups
+// are mapped so that the sites of a block run on one XCD, whose L2 then
+// serves the block's vectors to all of them.  Bound by the matrix cores' FP32
+// rate (16 x 16 tiles hold 40 x 12 results) and the latency of the chain step
+// size, inputs, product: 86 us for 12 fields on 4096 sites, d = 40, FP16
+// storage, against 230 us on the vector units; the residual (k_capply_mfma)
+// 136 against 194 us.
+template <typename S, int NJ>
+__global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_sap_q_mfma(CoarseOpView<float, S> op, const int* __restrict__ csites,
+                                                              SapTables tb, int pos0, int step,
+                                                              const float2* __restrict__ rho_prev,
+                                                              const float2* __restrict__ q_prev,
+                                                              const float* __restrict__ part_prev,
+                                                              float2* __restrict__ rho_cur,
+                                                              float2* __restrict__ q_cur, float* __restrict__ part_cur,
+                                                              float2* __restrict__ z, long long n, int nb, int per) {
+  extern __shared__ float2 lds_b[];
+  constexpr int nmt = (NJ + 3) / 4;
+  __shared__ float2 alpha_s[MFMA_NB];
+  __shared__ float dot_s[nmt][3][MFMA_NB];
+  const int x = xcd_slab_index(blockIdx.x, gridDim.x);
+  const int site = csites[x], d = op.d;
+  const int w = wave_id(), lane = threadIdx.x & 63;
+  const long long off = (long long)blockIdx.y * per * n, pn = (long long)op.V * 4;
+  const long long poff = (long long)blockIdx.y * per * pn;
+  rho_prev += off;
+  q_prev += off;
+  rho_cur += off;
+  q_cur += off;
+  z += off;
+  part_prev += poff;
+  part_cur += poff;
+  const int nr = min(per, nb - (int)blockIdx.y * per), pitch = nr | 1;
+  const int kk = lane >> 4, rl = min(lane & 15, nr - 1);
+  const int pos = pos0 + x, blk = pos / tb.bs;
+  const unsigned mask = __builtin_amdgcn_readfirstlane(tb.inmask[pos]);
+  MfmaRows<S, NJ> mr;
+  mr.prefetch(op.K + (size_t)site * 9 * d * d, mask, min(w * 16 + (lane & 15), d - 1), kk, d);
+  const int* nb9 = op.nbr9 + (size_t)site * 9;
+  // the site's own rows of the previous residual and of z, for z += alpha rho
+  const long long own = (long long)site * d + rl * n;
+  float2 zown[4], rown[4];
+  if (step > 0) {
+    mfma_rows(w, lane, d, [&](int v, int i) {
+      zown[v] = z[own + i];
+      rown[v] = rho_prev[own + i];
+    });
+    mfma_stage<NJ>(
+        lds_b, pitch, mask, nb9, w, nmt, lane, d, nr,
+        [&](int r, unsigned o) {
+          const float2 a = rho_prev[r * n + o], b = q_prev[r * n + o];
+          return make_float4(a.x, a.y, b.x, b.y);
+        },
+        [&](int r, float4 v) { return csub(make_float2(v.x, v.y), cmul(alpha_s[r], make_float2(v.z, v.w))); },
+        [&] {
+          for (int r0 = 4 * w; r0 < nr; r0 += 4 * nmt) {
+            const int r = min(r0 + (lane >> 4), nr - 1);
+            const float2 al = block_alpha_row(part_prev + r * pn, blk, tb.bs, lane);
+            if ((lane & 15) == 0) alpha_s[r] = al;
+          }
+          __syncthreads();
+        });
+  } else {
+    mfma_stage<NJ>(
+        lds_b, pitch, mask, nb9, w, nmt, lane, d, nr, [&](int r, unsigned o) { return rho_prev[r * n + o]; },
+        [](int, float2 v) { return v; }, [] {});
+  }
+  __syncthreads();
+  f32x4 cr, ci;
+  mr.apply(lds_b, pitch, rl, cr, ci);
+  float a0 = 0.f, a1 = 0.f, a2 = 0.f;
+  const bool live = (lane & 15) < nr;
+  mfma_rows(w, lane, d, [&](int v, int i) {
+    const float2 rho = lds_b[i * pitch + rl], q = make_float2(cr[v], ci[v]);
+    a0 = rfma(q.x, rho.x, rfma(q.y, rho.y, a0));
+    a1 = rfma(q.x, rho.y, rfma(-q.y, rho.x, a1));
+    a2 = rfma(q.x, q.x, rfma(q.y, q.y, a2));
+    if (live) {
+      rho_cur[own + i] = rho;
+      q_cur[own + i] = q;
+      if (step > 0) {
+        cfma(zown[v], alpha_s[rl], rown[v]);
+        z[own + i] = zown[v];
+      }
+    }
+  });
+  // over the four row groups of the tile, then over the wavefronts
+  a0 += __shfl_xor(a0, 16, 64);
+  a1 += __shfl_xor(a1, 16, 64);
+  a2 += __shfl_xor(a2, 16, 64);
+  a0 += __shfl_xor(a0, 32, 64);
+  a1 += __shfl_xor(a1, 32, 64);
+  a2 += __shfl_xor(a2, 32, 64);
+  if (lane < 16) {
+    dot_s[w][0][lane] = a0;
+    dot_s[w][1][lane] = a1;
+    dot_s[w][2][lane] = a2;
+  }
+  __syncthreads();
+  for (int e = threadIdx.x; e < 3 * nr; e += 64 * nmt) {
+    const int c = e / nr, r = e - c * nr;
+    float t = 0.f;
+#pragma unroll
+    for (int v = 0; v < nmt; ++v) t += dot_s[v][c][r];
+    part_cur[r * pn + (size_t)pos * 4 + c] = t;
+  }
+}
+
 template <typename T>
 __global__ void k_sap_fin(int d, const int* __restrict__ csites, SapTables tb, int pos0,
                           const C<T>* __restrict__ rho, const T* __restrict__ part, C<T>* __restrict__ z, long long n,
@@ -731,6 +979,23 @@ void coarse_sap_colour(const CoarseOpView<T, S>& op, const SapTables& tb, int co
   const int pos0 = colour * (tb.nblk / 2) * tb.bs;   // blocks are colour-major
   const int* csites = tb.blk_sites + pos0;
   const long long n = (long long)op.V * op.d, pn = (long long)op.V * 4;
+  bool done = false;
+  if constexpr (std::is_same<T, float>::value) {
+    if (use_mfma(nb)) {
+      coarse_apply_mfma<S>(op, csites, nsites, z, b, ws.rho[1], s, nb);
+      const MfmaShape m = mfma_shape(op.d, nb, tb.kmax);
+      for (int t = 0; t < mr_iters; ++t) {
+        const int pp = (t + 1) & 1, cc = t & 1;   // previous / current buffers
+        with_int<1, 16>(m.nj, [&](auto nj) {
+          k_sap_q_mfma<S, decltype(nj)::value><<<dim3(nsites, m.nch), 64 * m.nmt, m.lds, s>>>(
+              op, csites, tb, pos0, t, ws.rho[pp], ws.q[pp], ws.part[pp], ws.rho[cc], ws.q[cc], ws.part[cc], z, n, nb,
+              m.per);
+        });
+      }
+      done = true;
+    }
+  }
+  if (!done)
   with_nch(op.d, [&](auto nch) {
     constexpr int NCH = decltype(nch)::value;
     rhs_chunks<T>(nb, [&](auto rb, int first, int nc) {

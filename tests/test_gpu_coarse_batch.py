@@ -1,0 +1,67 @@
+"""Batched coarse-level operator and SAP smoother on the matrix cores, against
+the FP64 oracle on the operator the kernels store (rounded to FP16 where the
+hierarchy has FP16 storage, so that only the arithmetic differs).
+
+Sizes: components per site that fill their 16-row tiles (64), end inside one
+(40, 56) or inside a step of four columns (26); batches at the edges of the
+dispatch and of a 16-field chunk; SAP blocks of 16 sites and of one site.
+
+Tolerance: a component is a sum of 9d complex products in FP32, whose rounding
+errors add to about sqrt(4 * 9d) 2^-24 <= 3e-6 of it; a smoother step stacks a
+few such products: 1e-5 for both."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle.sap import smooth
+from oracle.stencil import BlockStencil
+from tests.gpu_util import dev, empty, export_Dc, host, relerr, say, to_params
+from tests.test_gpu_hierarchy import _p
+
+pytestmark = pytest.mark.gpu
+
+DIMS = (16, 16, 16, 16)
+TOL = 1e-5
+
+
+@pytest.fixture(scope="module")
+def dd():
+    from paper_1307_6101_amd import ddamg
+    ddamg.load_library()
+    return ddamg
+
+
+def _half(a):
+    return a.real.astype(np.float16).astype(np.float64) + 1j * a.imag.astype(np.float16).astype(np.float64)
+
+
+@pytest.mark.parametrize("n,half,nrhs", [(20, False, (3, 17)), (20, True, (5, 16)), (13, True, (3,)), (28, False, (16,)),
+                                         (32, True, (3, 14))])
+def test_batched_coarse_level(dd, n, half, nrhs):
+    say(f"coarse batch d={2 * n} half={half} nrhs={nrhs}")
+    p = _p(3, [(4, 4, 4, 4), (2, 2, 2, 2)], [n, 4], n_inv=0)
+    ctx = dd.create(DIMS, -0.3, 1.0, dev(W.links(DIMS, 0.5, 71)))
+    H = dd.build_hierarchy(ctx, to_params(dd, p, dd.F32, half=half), dev(W.test_vectors(DIMS, 12, n, 72)))
+    G = export_Dc(dd, H, 1)
+    if half:
+        G = _half(G)
+    op = BlockStencil((4, 4, 4, 4), G[..., 0, :, :], np.moveaxis(G[..., 1:5, :, :], -3, 0),
+                      np.moveaxis(G[..., 5:9, :, :], -3, 0))
+    for nb in nrhs:
+        b = W.gaussian_field(op.dims, op.d, 80 + nb, nrhs=nb)
+        z0 = 0.3 * W.gaussian_field(op.dims, op.d, 81 + nb, nrhs=nb)
+        out = empty(b.shape)
+        dd.apply_Dc(H, 1, dev(b), out, nrhs=nb, prec=dd.F32)
+        got = host(out)
+        for r in range(nb):
+            assert relerr(got[r], op.apply(b[r])) <= TOL, (nb, r)
+        for block in ((2, 2, 2, 2), (1, 1, 1, 1)):
+            dd.set_sap_block(H, 1, block)
+            z = dev(z0)
+            dd.sap_smooth(H, 1, dev(b), z, 2, nrhs=nb, prec=dd.F32)
+            got = host(z)
+            e = max(relerr(got[r], smooth(op, b[r], z0[r], 2, block)) for r in range(nb))
+            say(f"  nrhs={nb} block={block} relerr {e:.2e}")
+            assert e <= TOL
+    torch.cuda.synchronize()
