@@ -1227,15 +1227,24 @@ __global__ void k_self_inverse(const double2* __restrict__ D5, const int* __rest
   }
   __syncthreads();
   for (int col = 0; col < d; ++col) {
-    if (threadIdx.x == 0) {
-      int best = col;
+    if (threadIdx.x < 64) {
+      // the first of the largest entries at or below the diagonal (a NaN is
+      // never chosen), lane r looking at row r
+      const int r = threadIdx.x;
       double bv = -1.0;
-      for (int r = col; r < d; ++r) {
+      int best = col;
+      if (r >= col && r < d) {
         const double2 v = a[r * w + col];
         const double m = v.x * v.x + v.y * v.y;
         if (m > bv) { bv = m; best = r; }
       }
-      piv = best;
+#pragma unroll
+      for (int off = 32; off > 0; off >>= 1) {
+        const double ov = __shfl_xor(bv, off, 64);
+        const int ob = __shfl_xor(best, off, 64);
+        if (ov > bv || (ov == bv && ob < best)) { bv = ov; best = ob; }
+      }
+      if (r == 0) piv = best;
     }
     __syncthreads();
     if (piv != col)

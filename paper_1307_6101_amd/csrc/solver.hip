@@ -1237,10 +1237,9 @@ void Hierarchy::build_level(int l, bool from32) {
   if (from32) vcopy<float, double>(F.tv32.p, F.tv64.p, (long long)N * n, s);
   if (!setup_flags.p) setup_flags.alloc(2);
   DD_CHECK_HIP(hipMemsetAsync(setup_flags.p, 0, 2 * sizeof(int), s));
-  if (l == 0) orthonormalise_fine(ctx->g, F.at, F.ad(), N, F.tv64.p, F.P64.p, setup_flags.p, s);
-  else orthonormalise_coarse(F.at, F.ad(), F.d, N, F.V, F.tv64.p, F.P64.p, setup_flags.p, s);
-  if (F.P32.p) vcopy<double, float>(F.P64.p, F.P32.p, (long long)N * n, s);
-  if (F.P16.p) to_half(F.P64.p, F.P16.p, (long long)N * n, s);
+  // (and its stored copy in FP32 or FP16)
+  if (l == 0) orthonormalise_fine(ctx->g, F.at, F.ad(), N, F.tv64.p, F.P64.p, F.P32.p, F.P16.p, setup_flags.p, s);
+  else orthonormalise_coarse(F.at, F.ad(), F.d, N, F.V, F.tv64.p, F.P64.p, F.P32.p, F.P16.p, setup_flags.p, s);
   // Galerkin in FP64
   if (l == 0) galerkin_fine(ctx->g, F.at, F.ad(), N, ctx->view<double>(), F.P64.p, Cc.D64.p, s);
   else galerkin_coarse(F.cg, F.at, F.ad(), N, F.cview<double>(), F.P64.p, Cc.D64.p, s, p.galerkin_cols);

@@ -509,13 +509,9 @@ void prolong_coarse(const AggTables& a, const AggDev& ad, int d, int N, long lon
 }
 
 // ---------------------------------------------------------------------------
-// Block orthonormalisation (FP64).  One workgroup per (aggregate, chirality);
-// every thread owns the same element positions in all N fields, so a thread
-// only re-reads what it wrote itself.  Gram-Schmidt with one full
-// re-orthogonalisation pass, in index order.
+// Block orthonormalisation (FP64)
 // ---------------------------------------------------------------------------
 constexpr int NMAX = 32;   // max test vectors per level
-constexpr int EPT = 8;     // max elements per thread
 
 // Element e of the restriction of a field to (aggregate A, chirality sigma):
 // the order is free (the result does not depend on it) and is chosen so that
@@ -540,168 +536,212 @@ struct CoarseMap {
   }
 };
 
+typedef double f64x4 __attribute__((ext_vector_type(4)));
+// Operand layout of v_mfma_f64_16x16x4f64: lane l supplies A[l % 16][l / 16] and
+// B[l / 16][l % 16]; result register v of lane l is D[l / 16 + 4 v][l % 16].
+__device__ inline f64x4 mfma4(double a, double b, f64x4 c) { return __builtin_amdgcn_mfma_f64_16x16x4f64(a, b, c, 0, 0, 0); }
+
 // Orthonormalisation of the N test vectors restricted to (aggregate,
 // chirality): one workgroup per pair, Cholesky QR applied twice.  A pass
-// forms the Gram matrix G = V^H V (chunks of the vectors staged in LDS,
-// one upper-triangle entry per thread), factors G = R^H R (R upper
-// triangular, positive diagonal), and writes V R^-1.  The Q factor with
-// positive diagonal R is unique, so this is the Gram-Schmidt result of the
-// paper's construction up to rounding; the second pass restores
-// orthogonality to working precision.  A vector that depends on the
-// earlier ones (zero pivot) gives a zero column, as Gram-Schmidt does.
-constexpr int ORTH_CHUNK = 16;    // elements per LDS chunk of the Gram pass
-constexpr int ORTH_APPLY = 64;    // elements per LDS chunk of the V R^-1 pass
-
-__device__ inline void orth_pair(int p, int N, int& i, int& j) {
-  // p -> (i, j), i <= j, row by row of the upper triangle
-  i = 0;
-  int row = N;
-  while (p >= row) {
-    p -= row;
-    --row;
-    ++i;
-  }
-  j = i + p;
-}
-
-template <class Map>
+// forms the Gram matrix G = V^H V, factors G = R^H R (R upper triangular,
+// positive diagonal), and writes V R^-1.  The Q factor with positive diagonal
+// R is unique, so this is the Gram-Schmidt result of the paper's construction
+// up to rounding; the second pass restores orthogonality to working
+// precision.  A vector that depends on the earlier ones (zero pivot) gives a
+// zero column, as Gram-Schmidt does.
+// Both products run on the FP64 matrix cores straight from memory: for the
+// Gram matrix a lane's element serves as operand of both sides, for V R^-1
+// the columns of R^-1 stay in registers and a tile of 16 elements is read
+// whole before it is written (the second pass works in place).  Bound by
+// memory: four reads and two writes of the vectors.  512 aggregates of 256
+// sites, N = 20: 2057 us with the products on the vector units from LDS,
+// 960 us so.  The last pass also writes the stored copy of P (FP32 or
+// FP16), where there is one, instead of a pass over P of its own.
+template <class Map, int MT>
 __global__ void __launch_bounds__(256) k_orth(Map map, int m, int N, long long fstride,
                                               const double2* __restrict__ tv, double2* __restrict__ P,
+                                              float2* __restrict__ P32, __half2* __restrict__ P16,
                                               int* __restrict__ flag) {
-  __shared__ double2 chunk[NMAX * ORTH_APPLY];
-  __shared__ double2 R[NMAX * NMAX];   // Gram matrix, then R (upper triangle)
-  __shared__ double2 X[NMAX * NMAX];   // R^-1 (upper triangle)
-  __shared__ int dep[NMAX];
+  constexpr int NT = 16 * MT, KS = 4 * MT;
+  __shared__ double2 R[NT][NT + 1];   // Gram matrix, then R (upper triangle)
+  __shared__ double2 X[NT][NT + 1];   // R^-1 (upper triangle)
+  __shared__ double diag[NT];
+  __shared__ int dep[NT];
   const int A = blockIdx.x >> 1, sigma = blockIdx.x & 1;
-  const int t = threadIdx.x;
-  const int npairs = N * (N + 1) / 2;
-  constexpr int PPT = (NMAX * (NMAX + 1) / 2 + 255) / 256;
+  const int t = threadIdx.x, w = t >> 6, lane = t & 63, n = lane & 15, kk = lane >> 4;
   for (int pass = 0; pass < 2; ++pass) {
     const double2* src = pass == 0 ? tv : P;
-    // Gram matrix
-    double2 acc[PPT];
-    int pi[PPT], pj[PPT];
+    // Gram matrix: tiles (0,0), (0,1), (1,1); wavefront w takes every fourth
+    // run of 16 elements
+    constexpr int TI = MT == 1 ? 1 : 3;
+    f64x4 gr[TI], gi[TI];
 #pragma unroll
-    for (int r = 0; r < PPT; ++r) {
-      acc[r] = czero<double>();
-      pi[r] = pj[r] = 0;
-      if (t + 256 * r < npairs) orth_pair(t + 256 * r, N, pi[r], pj[r]);
-    }
-    for (int e0 = 0; e0 < m; e0 += ORTH_CHUNK) {
-      for (int idx = t; idx < N * ORTH_CHUNK; idx += 256) {
-        const int j = idx / ORTH_CHUNK, e = e0 + idx % ORTH_CHUNK;
-        chunk[idx] = e < m ? src[j * fstride + map(A, sigma, e)] : czero<double>();
-      }
-      __syncthreads();
+    for (int q = 0; q < TI; ++q) gr[q] = gi[q] = f64x4{0, 0, 0, 0};
+    for (int e0 = 16 * w; e0 < m; e0 += 64) {
+      double2 v[4][MT];
 #pragma unroll
-      for (int r = 0; r < PPT; ++r)
-        if (t + 256 * r < npairs) {
-          const double2* a = chunk + pi[r] * ORTH_CHUNK;
-          const double2* b = chunk + pj[r] * ORTH_CHUNK;
+      for (int u = 0; u < 4; ++u) {
+        const int e = e0 + 4 * u + kk;
+        const long long o = map(A, sigma, min(e, m - 1));
 #pragma unroll
-          for (int q = 0; q < ORTH_CHUNK; ++q) cjfma(acc[r], a[q], b[q]);
+        for (int c = 0; c < MT; ++c) {
+          v[u][c] = src[min(16 * c + n, N - 1) * fstride + o];
+          if (e >= m) v[u][c] = czero<double>();
         }
+      }
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+#pragma unroll
+        for (int q = 0; q < TI; ++q) {
+          const double2 a = v[u][q / 2], b = v[u][(q + 1) / 2];
+          gr[q] = mfma4(a.x, b.x, gr[q]);
+          gi[q] = mfma4(a.x, b.y, gi[q]);
+          gr[q] = mfma4(a.y, b.y, gr[q]);
+          gi[q] = mfma4(-a.y, b.x, gi[q]);
+        }
+    }
+    // summed over the wavefronts in order
+    for (int v = 0; v < 4; ++v) {
+      if (v == w)
+#pragma unroll
+        for (int q = 0; q < TI; ++q)
+#pragma unroll
+          for (int k = 0; k < 4; ++k) {
+            double2& g = R[16 * (q / 2) + kk + 4 * k][16 * ((q + 1) / 2) + n];
+            const double2 add = make_double2(gr[q][k], gi[q][k]);
+            g = v == 0 ? add : cadd(g, add);
+          }
       __syncthreads();
     }
-#pragma unroll
-    for (int r = 0; r < PPT; ++r)
-      if (t + 256 * r < npairs) R[pi[r] * NMAX + pj[r]] = acc[r];
-    __syncthreads();
-    // Cholesky G = R^H R in place (upper triangle): thread j < N owns
-    // column j; step k fixes row k
+    if (t < NT) diag[t] = R[t][t].x;
+    // Cholesky G = R^H R in place (upper triangle): step k fixes row k and
+    // takes it out of the rows below
     for (int k = 0; k < N; ++k) {
-      if (t == k) {
-        double dk = R[k * NMAX + k].x;
-        for (int i = 0; i < k; ++i) {
-          const double2 r = R[i * NMAX + k];
-          dk -= r.x * r.x + r.y * r.y;
-        }
-        const double gkk = R[k * NMAX + k].x;
-        // a column whose part orthogonal to the earlier ones is below the
-        // rounding level of the Gram matrix (relative 1e-12) cannot be
-        // orthonormalised accurately from it: reported to the host
-        if (!(dk > 1e-12 * gkk)) *flag = 1;
-        const bool zero = !(gkk > 0.0) || !(dk > 1e-28 * gkk);
+      __syncthreads();
+      const double dk = R[k][k].x, gkk = diag[k];
+      // a column whose part orthogonal to the earlier ones is below the
+      // rounding level of the Gram matrix (relative 1e-12) cannot be
+      // orthonormalised accurately from it: reported to the host
+      if (t == 0 && !(dk > 1e-12 * gkk)) *flag = 1;
+      const bool zero = !(gkk > 0.0) || !(dk > 1e-28 * gkk);
+      const double rkk = zero ? 0.0 : sqrt(dk);
+      __syncthreads();
+      if (t == 0) {
         dep[k] = zero ? 1 : 0;
-        R[k * NMAX + k] = make_double2(zero ? 0.0 : sqrt(dk), 0.0);
+        R[k][k] = make_double2(rkk, 0.0);
       }
+      if (t > k && t < N) R[k][t] = zero ? czero<double>() : cscale(R[k][t], 1.0 / rkk);
       __syncthreads();
-      if (t > k && t < N) {
-        double2 g = R[k * NMAX + t];
-        for (int i = 0; i < k; ++i) g = csub(g, cjmul(R[i * NMAX + k], R[i * NMAX + t]));
-        const double rkk = R[k * NMAX + k].x;
-        R[k * NMAX + t] = rkk > 0.0 ? cscale(g, 1.0 / rkk) : czero<double>();
+      for (int e = t; e < NT * NT; e += 256) {
+        const int i = e / NT, j = e % NT;
+        if (i > k && j >= i && j < N) R[i][j] = csub(R[i][j], cjmul(R[k][i], R[k][j]));
       }
-      __syncthreads();
     }
+    __syncthreads();
     // X = R^-1: thread j < N solves column j (zero rows and columns for
-    // dependent vectors)
-    if (t < N) {
+    // dependent vectors and past N)
+    if (t < NT) {
       const int j = t;
-      for (int i = 0; i < N; ++i) X[i * NMAX + j] = czero<double>();
-      if (!dep[j]) {
-        X[j * NMAX + j] = make_double2(1.0 / R[j * NMAX + j].x, 0.0);
+      for (int i = 0; i < NT; ++i) X[i][j] = czero<double>();
+      if (j < N && !dep[j]) {
+        X[j][j] = make_double2(1.0 / R[j][j].x, 0.0);
         for (int i = j - 1; i >= 0; --i) {
           if (dep[i]) continue;
           double2 sacc = czero<double>();
-          for (int k = i + 1; k <= j; ++k) cfma(sacc, R[i * NMAX + k], X[k * NMAX + j]);
-          X[i * NMAX + j] = cscale(sacc, -1.0 / R[i * NMAX + i].x);
+          for (int k = i + 1; k <= j; ++k) cfma(sacc, R[i][k], X[k][j]);
+          X[i][j] = cscale(sacc, -1.0 / R[i][i].x);
         }
       }
     }
     __syncthreads();
-    // P = V X, chunks of ORTH_APPLY elements staged in LDS (the whole
-    // chunk is read before any of it is written, so the second pass may
-    // work in place); thread t forms outputs (element, column) t, t+256, ...
-    for (int e0 = 0; e0 < m; e0 += ORTH_APPLY) {
-      for (int idx = t; idx < N * ORTH_APPLY; idx += 256) {
-        const int j = idx / ORTH_APPLY, e = e0 + idx % ORTH_APPLY;
-        chunk[idx] = e < m ? src[j * fstride + map(A, sigma, e)] : czero<double>();
+    // P^T = X^T V^T by tiles of 16 elements; column tile c needs the vectors
+    // i < 16 (c + 1)
+    double2 x[MT][KS];
+#pragma unroll
+    for (int c = 0; c < MT; ++c)
+#pragma unroll
+      for (int q = 0; q < KS; ++q) x[c][q] = X[4 * q + kk][16 * c + n];
+    for (int e0 = 16 * w; e0 < m; e0 += 64) {
+      const int e = e0 + n;
+      const long long o = map(A, sigma, min(e, m - 1));
+      double2 v[KS];
+#pragma unroll
+      for (int q = 0; q < KS; ++q) v[q] = src[min(4 * q + kk, N - 1) * fstride + o];
+#pragma unroll
+      for (int c = 0; c < MT; ++c) {
+        f64x4 pr = {0, 0, 0, 0}, pi = {0, 0, 0, 0};
+#pragma unroll
+        for (int q = 0; q < 4 * (c + 1); ++q)
+          if (4 * q < N) {
+            pr = mfma4(x[c][q].x, v[q].x, pr);
+            pi = mfma4(x[c][q].x, v[q].y, pi);
+            pr = mfma4(-x[c][q].y, v[q].y, pr);
+            pi = mfma4(x[c][q].y, v[q].x, pi);
+          }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+          const int j = 16 * c + kk + 4 * k;
+          if (j < N && e < m) {
+            P[j * fstride + o] = make_double2(pr[k], pi[k]);
+            if (pass == 1 && P32) P32[j * fstride + o] = make_float2((float)pr[k], (float)pi[k]);
+            if (pass == 1 && P16) P16[j * fstride + o] = __floats2half2_rn((float)pr[k], (float)pi[k]);
+          }
+        }
       }
-      __syncthreads();
-      for (int idx = t; idx < N * ORTH_APPLY; idx += 256) {
-        const int j = idx / ORTH_APPLY, q = idx % ORTH_APPLY, e = e0 + q;
-        if (e >= m) continue;
-        double2 o = czero<double>();
-        for (int i = 0; i <= j; ++i) cfma(o, chunk[i * ORTH_APPLY + q], X[i * NMAX + j]);
-        P[j * fstride + map(A, sigma, e)] = o;
-      }
-      __syncthreads();
     }
+    // the second pass reads what other wavefronts wrote
+    __threadfence_block();
+    __syncthreads();
   }
 }
 
-void orthonormalise_fine(const FineGeom& g, const AggTables& a, const AggDev& ad, int N,
-                         const double2* tv, double2* P, int* flag, hipStream_t s) {
-  const int m = a.asz * 6;
-  DD_REQUIRE(N <= NMAX, "too many test vectors");
+template <class Map>
+static void orthonormalise(const Map& map, int nagg, int m, int N, long long fstride, const double2* tv, double2* P,
+                           float2* P32, __half2* P16, int* flag, hipStream_t s) {
+  DD_REQUIRE(N >= 1 && N <= NMAX, "too many test vectors");
   DD_REQUIRE(N <= m, "more test vectors than the aggregate dimension");
-  DD_REQUIRE(m <= 256 * EPT, "aggregate too large");
-  k_orth<FineMap><<<2 * a.nagg, 256, 0, s>>>(FineMap{ad.members, a.asz / 16}, m, N,
-                                            (long long)g.nblk * 192, tv, P, flag);
+  if (N <= 16) k_orth<Map, 1><<<2 * nagg, 256, 0, s>>>(map, m, N, fstride, tv, P, P32, P16, flag);
+  else k_orth<Map, 2><<<2 * nagg, 256, 0, s>>>(map, m, N, fstride, tv, P, P32, P16, flag);
   DD_LAUNCH_CHECK();
 }
 
-void orthonormalise_coarse(const AggTables& a, const AggDev& ad, int d, int N, long long V,
-                           const double2* tv, double2* P, int* flag, hipStream_t s) {
-  const int m = a.asz * (d / 2);
-  DD_REQUIRE(N <= NMAX, "too many test vectors");
-  DD_REQUIRE(N <= m, "more test vectors than the aggregate dimension");
-  DD_REQUIRE(m <= 256 * EPT, "aggregate too large");
-  k_orth<CoarseMap><<<2 * a.nagg, 256, 0, s>>>(CoarseMap{ad.members, a.asz, d}, m, N, V * d, tv, P, flag);
-  DD_LAUNCH_CHECK();
+void orthonormalise_fine(const FineGeom& g, const AggTables& a, const AggDev& ad, int N, const double2* tv, double2* P,
+                         float2* P32, __half2* P16, int* flag, hipStream_t s) {
+  orthonormalise(FineMap{ad.members, a.asz / 16}, a.nagg, a.asz * 6, N, (long long)g.nblk * 192, tv, P, P32, P16, flag,
+                 s);
+}
+
+void orthonormalise_coarse(const AggTables& a, const AggDev& ad, int d, int N, long long V, const double2* tv,
+                           double2* P, float2* P32, __half2* P16, int* flag, hipStream_t s) {
+  orthonormalise(CoarseMap{ad.members, a.asz, d}, a.nagg, a.asz * (d / 2), N, V * d, tv, P, P32, P16, flag, s);
 }
 
 // ---------------------------------------------------------------------------
-// Galerkin, fine level: grid (aggregate, coarse column (sigma, k)), one
-// thread per fine site of the aggregate.  For the column u = P_k restricted
-// to chirality sigma the thread forms, in turn, the self part
-//   y = A(x) u(x) - 1/2 sum of the hops whose both ends lie in the aggregate
-// and the four forward face parts y = -1/2 (1-g_mu) U_mu(x) u(x+mu) (x+mu
-// outside), and projects each on the rows P_k'(x) (both chiralities).
+// Galerkin, fine level: D_c = P^H D P on the FP64 matrix cores.  Per
+// aggregate and 16 of the 2N columns u = P_k restricted to chirality sigma,
+// a workgroup forms, from the forward hops alone,
+//   y = 1/2 A(x) u(x) - 1/2 sum_mu (1-g_mu) U_mu(x) u(x+mu)  (x+mu inside)
+// and the four face parts y = -1/2 (1-g_mu) U_mu(x) u(x+mu) (x+mu outside),
+// and projects each on the rows P_k'(x) (both chiralities).  The backward
+// hops are the gamma5-adjoints of the forward ones, so the self block is
+// G + G5 G^H G5 with G the first projection (k_self_adjoint).
+// A wavefront takes four sites at a time: lane l forms y for site l / 16 and
+// column l % 16, which is the B operand of the projection as it stands, four
+// sites of one component being four steps of its contraction; the A operand,
+// conj P_k' at those sites, is read from memory.  Four wavefronts per
+// chirality of the rows (which halves the accumulators and y) take the quarters of one 2^4 block after the other for
+// the self part (summed through LDS), so that they meet in the caches, then
+// one face each.  The chirality
+// of a lane's column enters through the spins it loads and one phase per
+// spin, so a group may hold columns of both.
+// The matrix-core products (20 rows and 40 columns fill 32 x 48) need 0.5 ms
+// for 512 aggregates and N = 20; what it takes, 2.02 ms, goes to the latency
+// and the issue of the hops' loads at the two wavefronts per SIMD that 256
+// registers allow (128 or 168 registers spill: 4.7 and 3.0 ms; all chiralities
+// of the rows in one wavefront 2.2 ms; both hop directions 3.4 ms).  One
+// column per workgroup with a wavefront reduction per entry took 5.13 ms.
 // ---------------------------------------------------------------------------
 struct GalFineGeom {
-  int nb[4];
   int agg[4];
 };
 
@@ -719,128 +759,215 @@ __device__ inline bool agg_col_xcd(int bid, int nagg, int ncol, int& A, int& col
 }
 inline unsigned agg_col_grid(int nagg, int ncol) { return 8u * (unsigned)((nagg + 7) / 8) * (unsigned)ncol; }
 
-// y += -1/2 * hop of the column restricted to chirality SIGMA: the other
-// spinor half is a compile-time zero (not loaded), and the factor -1/2 is
-// applied to the input so that the hop accumulates straight into y
-template <int MU, bool FWD, int SIGMA>
-__device__ inline void gal_hop(const FineOpView<double>& op, const double2* __restrict__ Pk, int blk, int loc,
-                               double2 y[12]) {
+// The half SP of y += -1/2 * forward hop of direction MU of this lane's
+// column, of chirality sigma, at one site (zero where !live).  With h_s = psi_s
+// + c_s psi_Js (see fine.hip) only the psi_s (sigma = 0) or the psi_Js (sigma =
+// 1) are there: v = U psi of that spin goes to spin s (SP = 0) times 1 or c_s
+// and to spin J_s (SP = 1) times conj(c_s) or 1.
+template <int MU, int SP>
+__device__ inline void gal_hop(const FineOpView<double>& op, const double2* Pk, int sigma, int blk, int nbf, int loc,
+                               bool live, double2 y[6]) {
+  using Q = Proj<MU>;
   constexpr int bit = 1 << MU;
-  int nb;
-  if constexpr (FWD) nb = (loc & bit) ? op.nbr[blk * 8 + 2 * MU] : blk;
-  else nb = (loc & bit) ? blk : op.nbr[blk * 8 + 2 * MU + 1];
-  double2 psi[12], u[9];
+  const int nb = (loc & bit) ? nbf : blk;
   const double2* p = Pk + (long long)nb * 192 + (loc ^ bit);
+  const int s0 = sigma ? Q::J0 : 0, s1 = sigma ? Q::J1 : 1;
+  double2 h[6], u[9];
 #pragma unroll
-  for (int c = 0; c < 12; ++c)
-    psi[c] = (c / 6) == SIGMA ? cscale(p[c * 16], -0.5) : czero<double>();
-  if constexpr (FWD) load_link<double>(op.U, blk, loc, MU, u);
-  else load_link<double>(op.U, nb, loc ^ bit, MU, u);
-  hop_apply<double, MU, FWD>(psi, u, y);
-}
-
-template <int MU, int SIGMA>
-__device__ inline void gal_hops_inside(const FineOpView<double>& op, const double2* Pk, int blk, int loc,
-                                       const bool* fin, const bool* bin, double2 y[12]) {
-  if (fin[MU]) gal_hop<MU, true, SIGMA>(op, Pk, blk, loc, y);
-  if (bin[MU]) gal_hop<MU, false, SIGMA>(op, Pk, blk, loc, y);
-}
-
-// part tau of the column (SIGMA, k) at this thread's site: tau = 0 the self
-// part (clover and the hops inside the aggregate), tau = 1 + mu the forward
-// face part across the +mu face
-template <int SIGMA>
-__device__ inline void gal_part(const FineOpView<double>& op, const double2* __restrict__ Pk, int blk, int loc,
-                                const bool* fin, const bool* bin, int tau, double2 y[12]) {
-  if (tau == 0) {
-    // the clover is block diagonal in chirality: only block SIGMA acts
-    double2 u[6];
-    const double2* p = Pk + (long long)blk * 192 + loc + 6 * SIGMA * 16;
+  for (int a = 0; a < 3; ++a) {
+    h[a] = p[(s0 * 3 + a) * 16];
+    h[3 + a] = p[(s1 * 3 + a) * 16];
+  }
+  load_link<double>(op.U, blk, loc, MU, u);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) u[c] = p[c * 16];
+  for (int a = 0; a < 6; ++a) h[a] = live ? cscale(h[a], -0.5) : czero<double>();
+  const double2 one = make_double2(1.0, 0.0);
 #pragma unroll
-    for (int c = 0; c < 6; ++c) y[6 * (1 - SIGMA) + c] = czero<double>();
-    const double2* a = op.A + (long long)blk * 576 + loc;
-    clover_block<double>(SIGMA, [&](int e) { return a[e * 16]; }, u, y + 6 * SIGMA);
-    gal_hops_inside<0, SIGMA>(op, Pk, blk, loc, fin, bin, y);
-    gal_hops_inside<1, SIGMA>(op, Pk, blk, loc, fin, bin, y);
-    gal_hops_inside<2, SIGMA>(op, Pk, blk, loc, fin, bin, y);
-    gal_hops_inside<3, SIGMA>(op, Pk, blk, loc, fin, bin, y);
-  } else {
+  for (int s = 0; s < 2; ++s) {
+    const double2 c = s ? mul_ik<Q::K1>(one) : mul_ik<Q::K0>(one);
+    const double2 f = SP == 0 ? (sigma ? c : one) : (sigma ? one : cconj(c));
+    constexpr int O0 = SP == 0 ? 0 : (Q::J0 - 2) * 3, O1 = SP == 0 ? 3 : (Q::J1 - 2) * 3;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) y[c] = czero<double>();
-    const int mu = tau - 1;
-    if (!fin[mu]) {
-      if (mu == 0) gal_hop<0, true, SIGMA>(op, Pk, blk, loc, y);
-      else if (mu == 1) gal_hop<1, true, SIGMA>(op, Pk, blk, loc, y);
-      else if (mu == 2) gal_hop<2, true, SIGMA>(op, Pk, blk, loc, y);
-      else gal_hop<3, true, SIGMA>(op, Pk, blk, loc, y);
+    for (int a = 0; a < 3; ++a) {
+      double2 v = cmul(u[a * 3], h[s * 3]);
+      cfma(v, u[a * 3 + 1], h[s * 3 + 1]);
+      cfma(v, u[a * 3 + 2], h[s * 3 + 2]);
+      cfma(y[(s ? O1 : O0) + a], f, v);
     }
   }
 }
 
-__global__ void __launch_bounds__(256) k_galerkin_fine(GalFineGeom gg, const int* __restrict__ members,
-                                                       int nbpa, int N, int nagg, FineOpView<double> op,
-                                                       const double2* __restrict__ P, long long fstride,
-                                                       double2* __restrict__ Dc) {
-  __shared__ double red[4 * NMAX * 4];
-  int A, col;
-  if (!agg_col_xcd(blockIdx.x, nagg, 2 * N, A, col)) return;
-  const int sigma = col / N, k = col % N;
-  const int t = threadIdx.x;
-  const int blk = members[A * nbpa + (t >> 4)], loc = t & 15;
-  // fine coordinates -> which hops stay inside the aggregate
-  bool fin[4], bin[4];
-  {
-    int bcs[4];
-    block_decode(gg.nb, blk, bcs);
-    for (int mu = 0; mu < 4; ++mu) {
-      const int bc = bcs[mu];
-      const int x = 2 * bc + ((loc >> mu) & 1);
-      const int xm = x % gg.agg[mu];
-      fin[mu] = xm != gg.agg[mu] - 1;
-      bin[mu] = xm != 0;
-    }
-  }
-  const double2* Pk = P + k * fstride;
-  const int twoN = 2 * N;
+// One wavefront's share: quarter w of every block (part 0) and a face of
+// direction w (part 1), the rows of chirality SP
+template <int MT, int SP>
+__device__ __forceinline__ void galerkin_rows(const GalFineGeom& gg, const int* __restrict__ members, int N, int A,
+                                              int grp, const FineOpView<double>& op, const double2* P,
+                                              long long fstride, double2* Dc, int w, double (*red)[MT * 8][64]) {
+  const int twoN = 2 * N, lane = threadIdx.x & 63, n = lane & 15, s = lane >> 4;
+  const int col = grp * 16 + n, colc = min(col, twoN - 1);
+  const int sigma = colc >= N ? 1 : 0;
+  const double2* Pk = P + (colc - sigma * N) * fstride;
+  const double2* row[MT];
+#pragma unroll
+  for (int q = 0; q < MT; ++q) row[q] = P + min(16 * q + n, N - 1) * fstride + SP * 96;
+  const int bpa[4] = {gg.agg[0] >> 1, gg.agg[1] >> 1, gg.agg[2] >> 1, gg.agg[3] >> 1};
+  f64x4 cr[MT], ci[MT];
 #pragma unroll 1
-  for (int tau = 0; tau < 5; ++tau) {
-    double2 y[12];
-    if (sigma == 0) gal_part<0>(op, Pk, blk, loc, fin, bin, tau, y);
-    else gal_part<1>(op, Pk, blk, loc, fin, bin, tau, y);
-    // a face part is nonzero only on the aggregate's face sites: the other
-    // threads skip the loads of the rows of P and contribute zeros
-    const bool live = tau == 0 || !fin[tau - 1];
-#pragma unroll 2
-    for (int kp = 0; kp < N; ++kp) {
-      double2 p0 = czero<double>(), p1 = czero<double>();
-      if (live) {
-        double2 w[12];
-        load_spinor<double>(P + kp * fstride, blk, loc, w);
+  for (int part = 0; part < 2; ++part) {
 #pragma unroll
-        for (int c = 0; c < 6; ++c) {
-          cjfma(p0, w[c], y[c]);
-          cjfma(p1, w[6 + c], y[6 + c]);
+    for (int q = 0; q < MT; ++q) cr[q] = ci[q] = f64x4{0, 0, 0, 0};
+    const int ng = part == 0 ? 16 : 64 / gg.agg[w];
+#pragma unroll 1
+    for (int g = 0; g < ng; ++g) {
+      // this lane's site: block bi of the aggregate, local index loc
+      int bi, loc;
+      if (part == 0) {
+        bi = g;
+        loc = 4 * w + s;
+      } else {
+        // the sites with the last coordinate in direction w: three local bits,
+        // then the blocks of the other directions
+        int f = 4 * g + s, stride = 1;
+        loc = 1 << w;
+        bi = 0;
+#pragma unroll
+        for (int nu = 0; nu < 4; ++nu)
+          if (nu != w) {
+            loc |= (f & 1) << nu;
+            f >>= 1;
+          }
+#pragma unroll
+        for (int nu = 0; nu < 4; ++nu) {
+          if (nu != w) {
+            bi += stride * (f % bpa[nu]);
+            f /= bpa[nu];
+          } else {
+            bi += stride * (bpa[nu] - 1);
+          }
+          stride *= bpa[nu];
         }
       }
-      stash4<double>(red, N, kp, p0.x, p0.y, p1.x, p1.y);
+      const int blk = members[A * 16 + bi];
+      const int4* np = reinterpret_cast<const int4*>(op.nbr + (size_t)blk * 8);
+      const int4 na = np[0], nb = np[1];
+      double2 y[6];
+#pragma unroll
+      for (int c = 0; c < 6; ++c) y[c] = czero<double>();
+      unsigned live = 0xF;   // bit nu: the forward hop of direction nu belongs to this part
+      if (part == 0) {
+        int r = bi;
+        live = 0;
+#pragma unroll
+        for (int nu = 0; nu < 4; ++nu) {
+          live |= (2 * (r % bpa[nu]) + ((loc >> nu) & 1) != gg.agg[nu] - 1 ? 1u : 0u) << nu;
+          r /= bpa[nu];
+        }
+        // the clover is block diagonal in chirality
+        if (__any(sigma == SP)) {
+          double2 u[6], o[6];
+          const double2* p = Pk + (long long)blk * 192 + loc + SP * 96;
+          const double2* a = op.A + (long long)blk * 576 + loc + SP * 288;
+#pragma unroll
+          for (int c = 0; c < 6; ++c) u[c] = p[c * 16];
+          clover_block<double>(0, [&](int e) { return a[e * 16]; }, u, o);
+          if (sigma == SP)
+#pragma unroll
+            for (int c = 0; c < 6; ++c) y[c] = cscale(o[c], 0.5);
+        }
+      }
+      // one hop after the other in a loop that stays one: side by side their
+      // loads would not fit the registers
+#pragma unroll 1
+      for (int h = part == 0 ? 0 : w; h <= (part == 0 ? 3 : w); ++h) {
+        const bool on = (live >> h) & 1;
+        switch (h) {
+          case 0: gal_hop<0, SP>(op, Pk, sigma, blk, na.x, loc, on, y); break;
+          case 1: gal_hop<1, SP>(op, Pk, sigma, blk, na.z, loc, on, y); break;
+          case 2: gal_hop<2, SP>(op, Pk, sigma, blk, nb.x, loc, on, y); break;
+          default: gal_hop<3, SP>(op, Pk, sigma, blk, nb.z, loc, on, y); break;
+        }
+      }
+      // projection: row k' = 16 q + l % 16, the four sites as contraction
+      const long long at = (long long)blk * 192 + loc;
+      double2 a[MT][6];
+#pragma unroll
+      for (int q = 0; q < MT; ++q)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) a[q][c] = row[q][at + c * 16];
+#pragma unroll
+      for (int q = 0; q < MT; ++q)
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+          cr[q] = mfma4(a[q][c].x, y[c].x, cr[q]);
+          ci[q] = mfma4(a[q][c].x, y[c].y, ci[q]);
+          cr[q] = mfma4(a[q][c].y, y[c].y, cr[q]);
+          ci[q] = mfma4(-a[q][c].y, y[c].x, ci[q]);
+        }
     }
-    __syncthreads();
-    if (t < twoN)
-      Dc[(((long long)A * 5 + tau) * twoN + t) * twoN + col] = collect<double>(red, N, t / N, t % N);
-    __syncthreads();
+    if (part == 0) {
+      // the four quarters of the self part
+      if (w > 0)
+#pragma unroll
+        for (int q = 0; q < MT; ++q)
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            red[w - 1][8 * q + v][lane] = cr[q][v];
+            red[w - 1][8 * q + 4 + v][lane] = ci[q][v];
+          }
+      __syncthreads();
+      if (w > 0) continue;
+    }
+#pragma unroll
+    for (int q = 0; q < MT; ++q)
+#pragma unroll
+      for (int v = 0; v < 4; ++v) {
+        double2 o = make_double2(cr[q][v], ci[q][v]);
+        if (part == 0)
+#pragma unroll
+          for (int u = 0; u < 3; ++u) o = cadd(o, make_double2(red[u][8 * q + v][lane], red[u][8 * q + 4 + v][lane]));
+        const int kp = 16 * q + s + 4 * v, tau = part == 0 ? 0 : 1 + w;
+        if (kp < N && col < twoN) Dc[(((long long)A * 5 + tau) * twoN + SP * N + kp) * twoN + col] = o;
+      }
+  }
+}
+
+template <int MT>
+__global__ void __launch_bounds__(512, 2) k_galerkin_fine(GalFineGeom gg, const int* __restrict__ members, int N,
+                                                          int nagg, FineOpView<double> op, const double2* P,
+                                                          long long fstride, double2* Dc) {
+  __shared__ double red[2][3][MT * 8][64];
+  int A, grp;
+  if (!agg_col_xcd(blockIdx.x, nagg, (2 * N + 15) / 16, A, grp)) return;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  if (w < 4) galerkin_rows<MT, 0>(gg, members, N, A, grp, op, P, fstride, Dc, w, red[0]);
+  else galerkin_rows<MT, 1>(gg, members, N, A, grp, op, P, fstride, Dc, w - 4, red[1]);
+}
+
+// self block <- G + G5 G^H G5 for every aggregate
+__global__ void __launch_bounds__(256) k_self_adjoint(int twoN, double2* __restrict__ Dc) {
+  double2* S = Dc + (long long)blockIdx.x * 5 * twoN * twoN;
+  const int h = twoN / 2;
+  for (int e = threadIdx.x; e < twoN * twoN; e += blockDim.x) {
+    const int i = e / twoN, j = e % twoN;
+    if (i > j) continue;
+    const double2 a = S[i * twoN + j], b = S[j * twoN + i];
+    const double g = (i < h) == (j < h) ? 1.0 : -1.0;
+    S[i * twoN + j] = make_double2(a.x + g * b.x, a.y - g * b.y);
+    if (i != j) S[j * twoN + i] = make_double2(b.x + g * a.x, b.y - g * a.y);
   }
 }
 
 void galerkin_fine(const FineGeom& g, const AggTables& a, const AggDev& ad, int N,
                    const FineOpView<double>& op, const double2* P, double2* Dc, hipStream_t s) {
-  DD_REQUIRE(a.asz == 256, "fine Galerkin kernel expects 4^4-site aggregates");
-  DD_REQUIRE(N <= NMAX, "too many test vectors");
+  DD_REQUIRE(a.asz == 256, "fine Galerkin kernel expects aggregates of 256 sites");
+  DD_REQUIRE(N >= 1 && N <= NMAX, "too many test vectors");
   GalFineGeom gg;
-  for (int mu = 0; mu < 4; ++mu) { gg.nb[mu] = g.nb[mu]; gg.agg[mu] = a.agg[mu]; }
-  k_galerkin_fine<<<agg_col_grid(a.nagg, 2 * N), 256, 0, s>>>(gg, ad.members, a.asz / 16, N, a.nagg, op, P,
-                                                              (long long)g.nblk * 192, Dc);
+  for (int mu = 0; mu < 4; ++mu) gg.agg[mu] = a.agg[mu];
+  const unsigned grid = agg_col_grid(a.nagg, (2 * N + 15) / 16);
+  const long long fs = (long long)g.nblk * 192;
+  if (N <= 16) k_galerkin_fine<1><<<grid, 512, 0, s>>>(gg, ad.members, N, a.nagg, op, P, fs, Dc);
+  else k_galerkin_fine<2><<<grid, 512, 0, s>>>(gg, ad.members, N, a.nagg, op, P, fs, Dc);
+  k_self_adjoint<<<a.nagg, 256, 0, s>>>(2 * N, Dc);
   DD_LAUNCH_CHECK();
 }
 
