@@ -316,15 +316,20 @@ struct MfmaRows {
 #pragma unroll
       for (int u = 0; u < DEP; ++u)
         if (s0 + u < ns) {
+          // summed per block, then over the blocks: shorter chains of FP32
+          // additions than one running sum over all columns
+          f32x4 br = {0.f, 0.f, 0.f, 0.f}, bi = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
           for (int t = 0; t < NJ; ++t) {
             const float2 av = ldc<float, S>(a[u][t]);
             const float2 bv = bt[((s0 + u) * 4 * NJ + 4 * t) * pitch];
-            cr = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, cr, 0, 0, 0);
-            ci = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.y, ci, 0, 0, 0);
-            cr = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.y, cr, 0, 0, 0);
-            ci = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.x, ci, 0, 0, 0);
+            br = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.x, br, 0, 0, 0);
+            bi = __builtin_amdgcn_mfma_f32_16x16x4f32(av.x, bv.y, bi, 0, 0, 0);
+            br = __builtin_amdgcn_mfma_f32_16x16x4f32(-av.y, bv.y, br, 0, 0, 0);
+            bi = __builtin_amdgcn_mfma_f32_16x16x4f32(av.y, bv.x, bi, 0, 0, 0);
           }
+          cr += br;
+          ci += bi;
           if (s0 + u + DEP < ns) load(u, s0 + u + DEP);
         }
     }
