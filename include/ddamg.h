@@ -268,7 +268,7 @@ int ddamg_create(const ddamg_lattice* lat, const void* links, void* stream, ddam
  * receives the bytes a context on `lat` made by ddamg_create_ws keeps: the
  * links and clover term in FP64 and FP32 (Sec. 1 eq. (1)), their FP16 copies
  * when params is non-NULL with half_storage = 1, the neighbour tables, and
- * scratch for canonical-layout ddamg_apply_D calls of up to nrhs_max fields.
+ * scratch for DDAMG_F16S conversions of up to nrhs_max fields.
  * *hier_bytes (if non-NULL; needs params) receives the bytes a hierarchy built
  * with these params by ddamg_build_hierarchy_ws keeps: P_l, D_{l+1} and the
  * test vectors of every level (Sec. 2), the setup's work (Alg. 3 and 4), and
@@ -286,9 +286,8 @@ int ddamg_workspace_bytes(const ddamg_lattice* lat, const ddamg_params* params, 
  * keep it allocated until ddamg_destroy has returned).  params (nullable) and
  * nrhs_max must be those given to ddamg_workspace_bytes; EINVAL if ws_bytes is
  * below its *ctx_bytes.  Calls that need more than was counted (ddamg_cgnr's
- * vectors, ddamg_apply_D on more than nrhs_max fields in canonical layout)
- * take it from the rest of the workspace and fail with ENOMEM when it runs
- * out. */
+ * vectors, DDAMG_F16S conversions of more than nrhs_max fields) take it from
+ * the rest of the workspace and fail with ENOMEM when it runs out. */
 int ddamg_create_ws(const ddamg_lattice* lat, const void* links, const ddamg_params* params, int nrhs_max,
                     void* workspace, size_t ws_bytes, void* stream, ddamg_ctx* out);
 void ddamg_destroy(ddamg_ctx ctx);

@@ -94,7 +94,6 @@ void from_nat(Context& c, int l, long long n, int nrhs, const C<T>* in, double2*
 // fields first.
 template <typename T, bool HALF = false>
 void apply_D_impl(Context& c, const void* in, void* out, int nrhs, int layout, hipStream_t s) {
-  const long long n = c.g.V * 12;
   const auto op = [&] {
     if constexpr (HALF) {
       c.make_half(s);
@@ -106,11 +105,7 @@ void apply_D_impl(Context& c, const void* in, void* out, int nrhs, int layout, h
   if (layout == DDAMG_NATIVE) {
     dslash<T>(op, static_cast<const C<T>*>(in), static_cast<C<T>*>(out), s, nrhs);
   } else {
-    C<T>* a = ctx_scratch<T>(c, 0, n * nrhs);
-    C<T>* b = ctx_scratch<T>(c, 1, n * nrhs);
-    to_nat<T>(c, 0, n, nrhs, static_cast<const double2*>(in), a, s);
-    dslash<T>(op, a, b, s, nrhs);
-    from_nat<T>(c, 0, n, nrhs, b, static_cast<double2*>(out), s);
+    dslash_canonical<T>(c.g, op, static_cast<const double2*>(in), static_cast<double2*>(out), s, nrhs);
   }
 }
 

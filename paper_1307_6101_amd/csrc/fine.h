@@ -12,9 +12,11 @@
 // brick, whose neighbours are half as often outside it as those of a row of
 // blocks.
 //   spinor  [nblk][12][16]      component = spin*3 + colour
-//   links   [nblk][4][9][16]    U_mu(x) row-major, x the site of the block
-//   clover  [nblk][36][16]      per chirality 18 entries: 3 packed real
-//                               diagonal pairs, 15 upper off-diagonals
+//   links   [nblk][36/N][16][N]   entry 9 mu + 3 row + column of the site's
+//                               36 at chunk e / N, place e % N; N entries fill
+//                               16 bytes (N = 1 in FP64, 2 in FP32, 4 in FP16)
+//   clover  [nblk][36/N][16][N]   likewise; per chirality 18 entries: 3 packed
+//                               real diagonal pairs, 15 upper off-diagonals
 // The neighbour of local site l in direction +-mu is local site l ^ (1<<mu),
 // either in the same block or in the neighbouring block (table nbr_blk).
 #pragma once
@@ -114,9 +116,12 @@ void fine_to_native(const FineGeom& g, const double2* in, C<T>* out, int nrhs, h
 template <typename T>
 void fine_from_native(const FineGeom& g, const C<T>* in, double2* out, int nrhs, hipStream_t s);
 
-// links canonical complex128 -> native T
-template <typename T>
-void links_to_native(const FineGeom& g, const double2* links, C<T>* out, hipStream_t s);
+// links canonical complex128 -> native FP64
+void links_to_native(const FineGeom& g, const double2* links, double2* out, hipStream_t s);
+// native FP64 links or clover -> the layout and precision of storage S (float2,
+// __half2)
+template <typename S>
+void op_store(const FineGeom& g, const double2* in, S* out, hipStream_t s);
 // clover (+ (m0+4)) from canonical complex128 links, native FP64
 void clover_build(const FineGeom& g, const double2* links, double m0, double csw, double2* out,
                   hipStream_t s);
@@ -124,6 +129,11 @@ void clover_build(const FineGeom& g, const double2* links, double m0, double csw
 // out = D in for nb native fields (field r at offset r * nblk * 192)
 template <typename T, typename S>
 void dslash(const FineOpView<T, S>& op, const C<T>* in, C<T>* out, hipStream_t s, int nb = 1);
+
+// the same on canonical complex128 fields, computed at T
+template <typename T, typename S>
+void dslash_canonical(const FineGeom& g, const FineOpView<T, S>& op, const double2* in, double2* out, hipStream_t s,
+                      int nb = 1);
 
 // out = D in in FP64 for nb fields stored in FP16 with site scales (the form
 // of encode_sites): D applied to exactly the values the FP16 field stands for
@@ -141,9 +151,6 @@ void sap_colour(const FineOpView<T, S>& op, const int* colour_blocks, int colour
 // is re-encoded with each updated site's new scale
 void sap_colour_hs(const FineOpView<float, __half2>& op, const int* colour_blocks, int colour, int mr_iters,
                    const __half2* b, const float* bs, __half2* z, float* zs, hipStream_t s, int nb = 1);
-
-// FP64 -> FP16 copy of n complex numbers (operator storage)
-void to_half(const double2* in, __half2* out, long long n, hipStream_t s);
 
 // FP16 fine fields with one FP32 scale per site (the largest |re|, |im| of
 // the site's 12 components; entries stored divided by it), for nb fields:

@@ -116,14 +116,32 @@ __global__ void k_from_native(DevGeom g, const C<T>* __restrict__ in, double2* _
     out[off + i * 12 + c] = ccast<double>(in[off + ((long long)blk * 12 + c) * 16 + loc]);
 }
 
-template <typename T>
-__global__ void k_links_to_native(DevGeom g, const double2* __restrict__ in, C<T>* __restrict__ out) {
+__global__ void k_links_to_native(DevGeom g, const double2* __restrict__ in, double2* __restrict__ out) {
   long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
   if (i >= g.V) return;
   int blk, loc;
   canonical_to_native(g, i, blk, loc);
-  for (int e = 0; e < 36; ++e)
-    out[((long long)blk * 36 + e) * 16 + loc] = ccast<T>(in[i * 36 + e]);
+  for (int e = 0; e < 36; ++e) out[((long long)blk * 36 + e) * 16 + loc] = in[i * 36 + e];
+}
+
+template <typename S> __device__ inline S op_round(double2 v);
+template <> __device__ inline float2 op_round<float2>(double2 v) { return make_float2((float)v.x, (float)v.y); }
+template <> __device__ inline __half2 op_round<__half2>(double2 v) {
+  return __floats2half2_rn((float)v.x, (float)v.y);
+}
+// one thread per (block, chunk, site): FP64 entries in, one chunk out
+template <typename S>
+__global__ void k_op_store(const double2* __restrict__ in, S* __restrict__ out, long long n) {
+  constexpr int N = OpChunk<S>::N, NQ = 36 / N;
+  const long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int loc = (int)(i & 15);
+  const long long bq = i >> 4, blk = bq / NQ;
+  const int q = (int)(bq - blk * NQ);
+  OpChunk<S> c;
+#pragma unroll
+  for (int k = 0; k < N; ++k) c.v[k] = op_round<S>(in[(blk * 36 + q * N + k) * 16 + loc]);
+  reinterpret_cast<OpChunk<S>*>(out)[i] = c;
 }
 
 template <typename T>
@@ -138,11 +156,18 @@ void fine_from_native(const FineGeom& g, const C<T>* in, double2* out, int nrhs,
   k_from_native<T><<<grid, 256, 0, s>>>(devgeom(g), in, out);
   DD_LAUNCH_CHECK();
 }
-template <typename T>
-void links_to_native(const FineGeom& g, const double2* links, C<T>* out, hipStream_t s) {
-  k_links_to_native<T><<<nblocks(g.V, 256), 256, 0, s>>>(devgeom(g), links, out);
+void links_to_native(const FineGeom& g, const double2* links, double2* out, hipStream_t s) {
+  k_links_to_native<<<nblocks(g.V, 256), 256, 0, s>>>(devgeom(g), links, out);
   DD_LAUNCH_CHECK();
 }
+template <typename S>
+void op_store(const FineGeom& g, const double2* in, S* out, hipStream_t s) {
+  const long long n = g.V * (36 / OpChunk<S>::N);
+  k_op_store<S><<<nblocks(n, 256), 256, 0, s>>>(in, out, n);
+  DD_LAUNCH_CHECK();
+}
+template void op_store<float2>(const FineGeom&, const double2*, float2*, hipStream_t);
+template void op_store<__half2>(const FineGeom&, const double2*, __half2*, hipStream_t);
 
 // ---------------------------------------------------------------------------
 // clover construction (FP64, canonical links in, native packed out)
@@ -307,53 +332,126 @@ __device__ inline Nbr8 load_nbr8(const int* __restrict__ nbr, int blk) {
   return Nbr8{{a.x, a.y, a.z, a.w, b.x, b.y, b.z, b.w}};
 }
 
-// (the input field in spinor storage V: C<T>, or FP16 with site scales ins)
-template <typename T, typename S, typename V, int MU>
-__device__ inline void hops_mu(const FineOpView<T, S>& op, const V* __restrict__ in, const float* __restrict__ ins,
-                               int blk, int loc, const Nbr8& nb8, C<T> acc[12]) {
+// Completes the arithmetic that produces acc before the statements that
+// follow (empty asm statements that read and write it), so that the next
+// direction's loads are not all issued ahead of it: hoisting the eight hops'
+// loads would need more registers than the colour pass can hold at two
+// wavefronts per SIMD.
+template <typename T> __device__ inline void pin12(C<T> (&acc)[12]) {
+#pragma unroll
+  for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[c].x), "+v"(acc[c].y));
+}
+
+// A stencil kernel reads its input spinors through one of these: a native
+// field of storage V (C<T>, or FP16 with site scales)
+template <typename T, typename V>
+struct NativeIn {
+  static constexpr bool EAGER = false;
+  const V* in;
+  const float* ins;
+  __device__ inline void site(int blk, int loc, C<T> v[12]) const { load_site<T, V>(in, ins, blk, loc, v); }
+  // the spinor at the site's neighbour in direction MU, which lies in block nb
+  template <int MU, bool FWD> __device__ inline void hop(int nb, int loc, C<T> v[12]) const {
+    site(nb, loc ^ (1 << MU), v);
+  }
+};
+
+// or from a canonical complex128 field
+template <typename T>
+struct CanonIn {
+  static constexpr bool EAGER = true;
+  // field f, the site with index t (block * 16 + local) in the tile at tc
+  __device__ inline void place(const DevGeom& g, const double2* f, const int (&tc)[4], int t) {
+    in = f;
+    dims[0] = g.X, dims[1] = g.Y, dims[2] = g.Z, dims[3] = g.T;
+#pragma unroll
+    for (int mu = 0; mu < 4; ++mu) c[mu] = 4 * tc[mu] + 2 * ((t >> (4 + mu)) & 1) + ((t >> mu) & 1);
+    own = c[0] + (long long)g.X * (c[1] + (long long)g.Y * (c[2] + (long long)g.Z * c[3]));
+  }
+  const double2* in;
+  int c[4], dims[4];     // the site's coordinates, the lattice
+  long long own;         // its canonical index
+  __device__ inline void at(long long i, C<T> v[12]) const {
+#pragma unroll
+    for (int k = 0; k < 12; ++k) v[k] = ccast<T>(in[i * 12 + k]);
+  }
+  __device__ inline void site(int, int, C<T> v[12]) const { at(own, v); }
+  template <int MU, bool FWD> __device__ inline void hop(int, int, C<T> v[12]) const {
+    long long st = 1;
+#pragma unroll
+    for (int mu = 0; mu < MU; ++mu) st *= dims[mu];
+    if constexpr (FWD) at(c[MU] + 1 == dims[MU] ? own - (dims[MU] - 1) * st : own + st, v);
+    else at(c[MU] == 0 ? own + (dims[MU] - 1) * st : own - st, v);
+  }
+};
+
+// Completes a hop before the next one's loads are issued where nothing else
+// (an index to wait for) spaces them out and they would not fit the registers
+template <typename T, typename In> __device__ inline void hop_done(C<T> (&acc)[12]) {
+  if constexpr (In::EAGER) {
+    pin12<T>(acc);
+    asm volatile("" ::: "memory");
+  }
+}
+
+// both hops of direction MU
+template <typename T, typename S, int MU, typename In>
+__device__ inline void hops_mu(const FineOpView<T, S>& op, const In& in, int blk, int loc, const Nbr8& nb8,
+                               C<T> (&acc)[12]) {
   constexpr int bit = 1 << MU;
   C<T> psi[12], u[9];
   // forward: psi(x+mu), U_mu(x)
   {
     const int nb = (loc & bit) ? nb8.v[2 * MU] : blk;
-    load_site<T, V>(in, ins, nb, loc ^ bit, psi);
-    load_link<T, S>(op.U, blk, loc, MU, u);
+    in.template hop<MU, true>(nb, loc, psi);
+    load_link<T, MU, S>(op.U, blk, loc, u);
     hop_apply<T, MU, true>(psi, u, acc);
+    hop_done<T, In>(acc);
   }
   // backward: psi(x-mu), U_mu(x-mu)^H
   {
     const int nb = (loc & bit) ? blk : nb8.v[2 * MU + 1];
-    load_site<T, V>(in, ins, nb, loc ^ bit, psi);
-    load_link<T, S>(op.U, nb, loc ^ bit, MU, u);
+    in.template hop<MU, false>(nb, loc, psi);
+    load_link<T, MU, S>(op.U, nb, loc ^ bit, u);
     hop_apply<T, MU, false>(psi, u, acc);
+    hop_done<T, In>(acc);
   }
 }
 
-// out(x) = (D in)(x) for one site
-template <typename T, typename S, typename V = C<T>>
-__device__ inline void dslash_site(const FineOpView<T, S>& op, const V* __restrict__ in,
-                                   const float* __restrict__ ins, int blk, int loc, C<T> out[12]) {
+// acc = (D in)(x) at one site
+template <typename T, typename S, bool NT, typename In>
+__device__ inline void dslash_site(const FineOpView<T, S>& op, const In& in, int blk, int loc, C<T> (&acc)[12]) {
   const Nbr8 nb8 = load_nbr8(op.nbr, blk);
-  C<T> acc[12];
 #pragma unroll
   for (int c = 0; c < 12; ++c) acc[c] = czero<T>();
-  hops_mu<T, S, V, 0>(op, in, ins, blk, loc, nb8, acc);
-  hops_mu<T, S, V, 1>(op, in, ins, blk, loc, nb8, acc);
-  hops_mu<T, S, V, 2>(op, in, ins, blk, loc, nb8, acc);
-  hops_mu<T, S, V, 3>(op, in, ins, blk, loc, nb8, acc);
-  C<T> psi[12];
-  load_site<T, V>(in, ins, blk, loc, psi);
-  clover_apply<T, S>(op.A, blk, loc, psi, out);
+  hops_mu<T, S, 0>(op, in, blk, loc, nb8, acc);
+  hops_mu<T, S, 1>(op, in, blk, loc, nb8, acc);
+  hops_mu<T, S, 2>(op, in, blk, loc, nb8, acc);
+  hops_mu<T, S, 3>(op, in, blk, loc, nb8, acc);
+  C<T> psi[12], av[12];
+  in.site(blk, loc, psi);
+  clover_apply<T, S, NT>(op.A, blk, loc, psi, av);
 #pragma unroll
-  for (int c = 0; c < 12; ++c) {
-    out[c].x -= T(0.5) * acc[c].x;
-    out[c].y -= T(0.5) * acc[c].y;
-  }
+  for (int c = 0; c < 12; ++c) acc[c] = mk<T>(av[c].x - T(0.5) * acc[c].x, av[c].y - T(0.5) * acc[c].y);
+}
+
+// Whether one field's pass reads its operator data past the caches: where it
+// does not fit the last-level cache it would only push out what is reused
+// (the faces' spinors).  FP64 stencil on 32^3x64: 893 -> 837 us; where it fits
+// (16^3x32, FP32) a repeated call finds it there: 21.0 us against 23.1.
+constexpr double LLC_BYTES = 256e6;
+template <typename S> inline bool op_streams(int nblk, int nb) {
+  return nb == 1 && 72.0 * sizeof(S) * 16 * nblk > LLC_BYTES;
 }
 
 // One site per thread.  A batch of nb fields runs over a one-dimensional
-// grid of gx * nb workgroups with the XCD-aware batch mapping.
-template <typename T, typename S, typename V = C<T>>
+// grid of gx * nb workgroups with the XCD-aware batch mapping.  The result is
+// written past the caches, which keep the spinors and links that neighbouring
+// workgroups share: 12 fields of 16^3x32 in FP32 218 -> 209 us (inputs not in the
+// last-level cache; 193 -> 168 us where they are), one FP64 field of 32^3x64 843
+// -> 820 us.  (Several fields per thread on one load of the links cost occupancy:
+// 12 fields 204 us one by one, 208 two and 267 four at a time.)
+template <typename T, typename S, typename V, bool NT>
 __global__ void __launch_bounds__(256) k_dslash(FineOpView<T, S> op, const V* __restrict__ in,
                                                 const float* __restrict__ ins, C<T>* __restrict__ out,
                                                 long long fs, int gx, int nb) {
@@ -362,30 +460,184 @@ __global__ void __launch_bounds__(256) k_dslash(FineOpView<T, S> op, const V* __
   const int tid = x * blockDim.x + threadIdx.x;
   const int blk = tid >> 4, loc = tid & 15;
   if (blk >= op.nblk) return;
-  in += (long long)r * fs;
-  if constexpr (std::is_same<V, __half2>::value) ins += (long long)r * (fs / 12);
-  out += (long long)r * fs;
+  const long long off = (long long)r * fs;
   C<T> o[12];
-  dslash_site<T, S, V>(op, in, ins, blk, loc, o);
-  C<T>* p = out + (long long)blk * 192 + loc;
+  dslash_site<T, S, NT>(op, NativeIn<T, V>{in + off, std::is_same<V, __half2>::value ? ins + off / 12 : nullptr}, blk,
+                        loc, o);
+  C<T>* p = out + off + (long long)blk * 192 + loc;
 #pragma unroll
-  for (int c = 0; c < 12; ++c) p[c * 16] = o[c];
+  for (int c = 0; c < 12; ++c) store_nt(p + c * 16, o[c]);
+}
+
+// The stencil on canonical complex128 fields, without native copies of them:
+// a site's spinor is 192 contiguous bytes to read, and the workgroup's 4^4
+// tile of results goes through LDS to be written in rows of four sites (768
+// bytes).  FP64 on 48^3x96: 4334 us, against 6829 us with a conversion
+// before and after the native stencil (1264 and 1063 us).
+template <typename T, typename S, bool NT>
+__global__ void __launch_bounds__(256) k_dslash_canonical(FineOpView<T, S> op, DevGeom g,
+                                                          const double2* in, double2* out, int gx, int nb) {
+  constexpr int PITCH = 13;
+  __shared__ C<T> tile[256 * PITCH];
+  int x, r;
+  xcd_slab_rhs(blockIdx.x, gx, nb, x, r);
+  const int t = threadIdx.x, blk = x * 16 + (t >> 4), loc = t & 15;
+  const int nt[4] = {g.nb[0] >> 1, g.nb[1] >> 1, g.nb[2] >> 1, g.nb[3] >> 1};
+  int tc[4];
+  tile_decode(nt, x, tc);
+  CanonIn<T> f;
+  f.place(g, in + (long long)r * g.V * 12, tc, t);
+  C<T> o[12];
+  dslash_site<T, S, NT>(op, f, blk, loc, o);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) tile[t * PITCH + c] = o[c];
+  __syncthreads();
+  out += (long long)r * g.V * 12;
+#pragma unroll
+  for (int k = 0; k < 12; ++k) {
+    const int e = 256 * k + t, row = e / 48, q = e - 48 * row, xs = q / 12, c = q - 12 * xs;
+    const int ys = row & 3, zs = (row >> 2) & 3, ts = row >> 4;
+    const int src = (xs & 1) | (ys & 1) << 1 | (zs & 1) << 2 | (ts & 1) << 3 | (xs >> 1) << 4 | (ys >> 1) << 5 |
+                    (zs >> 1) << 6 | (ts >> 1) << 7;
+    const long long site = 4 * tc[0] + (long long)g.X * (4 * tc[1] + ys + (long long)g.Y * (4 * tc[2] + zs + (long long)g.Z * (4 * tc[3] + ts)));
+    store_nt(out + site * 12 + q, ccast<double>(tile[src * PITCH + c]));
+  }
+}
+
+// The stencil of a small lattice: four wavefronts share 64 sites, wavefront mu
+// doing both hops of direction mu (and two of them a chirality of the clover
+// each), summed through LDS.  w: the wavefront, lane: its site; on return
+// acc[3 w .. 3 w + 2] are those components of (D in)(x).
+template <typename T, typename S, typename In>
+__device__ inline void dslash_split_site(const FineOpView<T, S>& op, const In& f, int w, int lane, int blk, int loc,
+                                         C<T> (*part)[12][64], C<T> (&acc)[12]) {
+  const Nbr8 nb8 = load_nbr8(op.nbr, blk);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = czero<T>();
+  if (w == 0) hops_mu<T, S, 0>(op, f, blk, loc, nb8, acc);
+  else if (w == 1) hops_mu<T, S, 1>(op, f, blk, loc, nb8, acc);
+  else if (w == 2) hops_mu<T, S, 2>(op, f, blk, loc, nb8, acc);
+  else hops_mu<T, S, 3>(op, f, blk, loc, nb8, acc);
+#pragma unroll
+  for (int c = 0; c < 12; ++c) acc[c] = cscale(acc[c], T(-0.5));
+  if (w < 2) {
+    C<T> psi[12], av[6];
+    f.site(blk, loc, psi);
+    C<T> v[6];
+    S e[18];
+    if (w) load_entries<18, 18>(op.A, blk, loc, e);
+    else load_entries<0, 18>(op.A, blk, loc, e);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) v[c] = w ? psi[6 + c] : psi[c];
+    clover_block<T>(0, [&](int k) { return ldc<T, S>(e[k]); }, v, av);
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      if (w) acc[6 + c] = cadd(acc[6 + c], av[c]);
+      else acc[c] = cadd(acc[c], av[c]);
+    }
+  }
+  // wavefront w sums components 3w .. 3w + 2, its own from registers
+#pragma unroll
+  for (int c = 0; c < 12; ++c) {
+    const int o = c / 3;
+    if (o != w) part[o < w ? w - 1 : w][c][lane] = acc[c];
+  }
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < 12; ++c)
+    if (c / 3 == w)
+#pragma unroll
+      for (int k = 0; k < 3; ++k) acc[c] = cadd(acc[c], part[k][c][lane]);
+}
+
+// (grid: gx groups of four blocks per field; nblk is a multiple of 16)
+template <typename T, typename S, typename V>
+__global__ void __launch_bounds__(256) k_dslash_split(FineOpView<T, S> op, const V* __restrict__ in,
+                                                      const float* __restrict__ ins, C<T>* __restrict__ out,
+                                                      long long fs, int gx) {
+  __shared__ C<T> part[3][12][64];
+  const int x = blockIdx.x % gx, r = blockIdx.x / gx;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int blk = x * 4 + (lane >> 4), loc = lane & 15;
+  const long long off = r * fs;
+  C<T> acc[12];
+  dslash_split_site<T, S>(op, NativeIn<T, V>{in + off, std::is_same<V, __half2>::value ? ins + off / 12 : nullptr}, w,
+                          lane, blk, loc, part, acc);
+  C<T>* po = out + off + (long long)blk * 192 + loc;
+#pragma unroll
+  for (int c = 0; c < 12; ++c)
+    if (c / 3 == w) po[c * 16] = acc[c];
+}
+// the same on canonical fields
+template <typename T, typename S>
+__global__ void __launch_bounds__(256) k_dslash_split_canonical(FineOpView<T, S> op, DevGeom g, const double2* in,
+                                                                double2* out, int gx) {
+  __shared__ C<T> part[3][12][64];
+  const int x = blockIdx.x % gx, r = blockIdx.x / gx;
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = threadIdx.x & 63;
+  const int blk = x * 4 + (lane >> 4), loc = lane & 15;
+  const int nt[4] = {g.nb[0] >> 1, g.nb[1] >> 1, g.nb[2] >> 1, g.nb[3] >> 1};
+  int tc[4];
+  tile_decode(nt, x >> 2, tc);
+  CanonIn<T> f;
+  f.place(g, in + (long long)r * g.V * 12, tc, (blk & 15) * 16 + loc);
+  C<T> acc[12];
+  dslash_split_site<T, S>(op, f, w, lane, blk, loc, part, acc);
+  double2* po = out + ((long long)r * g.V + f.own) * 12;
+#pragma unroll
+  for (int c = 0; c < 12; ++c)
+    if (c / 3 == w) po[c] = ccast<double>(acc[c]);
+}
+
+// Largest grid (in workgroups of 256 sites) that is split: below it the device
+// is not filled and a call takes as long as one site's chain of loads.  Kernel
+// and launch in us, one site per thread / split, FP64: 4096 sites 9.3 / 7.4,
+// 16384 sites 10.1 / 8.8, 32768 sites 13.8 / 16.2.
+constexpr unsigned DSLASH_SPLIT = 64;
+
+template <typename T, typename S, typename V>
+static void dslash_launch(const FineOpView<T, S>& op, const V* in, const float* ins, C<T>* out, hipStream_t s, int nb) {
+  const long long fs = (long long)op.nblk * 192;
+  const unsigned gx = nblocks((size_t)op.nblk * 16, 256);
+  if (gx * nb <= DSLASH_SPLIT) {
+    const unsigned g4 = op.nblk / 4;
+    k_dslash_split<T, S, V><<<g4 * nb, 256, 0, s>>>(op, in, ins, out, fs, (int)g4);
+  } else if (op_streams<S>(op.nblk, nb)) {
+    k_dslash<T, S, V, true><<<gx * nb, 256, 0, s>>>(op, in, ins, out, fs, (int)gx, nb);
+  } else {
+    k_dslash<T, S, V, false><<<gx * nb, 256, 0, s>>>(op, in, ins, out, fs, (int)gx, nb);
+  }
+  DD_LAUNCH_CHECK();
 }
 
 template <typename T, typename S>
-void dslash(const FineOpView<T, S>& op, const C<T>* in, C<T>* out, hipStream_t s, int nb) {
-  const long long fs = (long long)op.nblk * 192;
-  const unsigned gx = nblocks((size_t)op.nblk * 16, 256);
-  k_dslash<T, S><<<gx * nb, 256, 0, s>>>(op, in, nullptr, out, fs, (int)gx, nb);
+void dslash_canonical(const FineGeom& g, const FineOpView<T, S>& op, const double2* in, double2* out, hipStream_t s,
+                      int nb) {
+  const unsigned gx = op.nblk / 16;
+  // (the same line as for native fields: both give the same bits)
+  if (gx * nb <= DSLASH_SPLIT)
+    k_dslash_split_canonical<T, S><<<4 * gx * nb, 256, 0, s>>>(op, devgeom(g), in, out, (int)(4 * gx));
+  else if (op_streams<S>(op.nblk, nb))
+    k_dslash_canonical<T, S, true><<<gx * nb, 256, 0, s>>>(op, devgeom(g), in, out, (int)gx, nb);
+  else
+    k_dslash_canonical<T, S, false><<<gx * nb, 256, 0, s>>>(op, devgeom(g), in, out, (int)gx, nb);
   DD_LAUNCH_CHECK();
+}
+template void dslash_canonical<double, double2>(const FineGeom&, const FineOpView<double>&, const double2*, double2*,
+                                                hipStream_t, int);
+template void dslash_canonical<float, float2>(const FineGeom&, const FineOpView<float>&, const double2*, double2*,
+                                              hipStream_t, int);
+template void dslash_canonical<float, __half2>(const FineGeom&, const FineOpView<float, __half2>&, const double2*,
+                                               double2*, hipStream_t, int);
+
+template <typename T, typename S>
+void dslash(const FineOpView<T, S>& op, const C<T>* in, C<T>* out, hipStream_t s, int nb) {
+  dslash_launch<T, S, C<T>>(op, in, nullptr, out, s, nb);
 }
 
 void dslash_hs(const FineOpView<double>& op, const __half2* in, const float* ins, double2* out, hipStream_t s,
                int nb) {
-  const long long fs = (long long)op.nblk * 192;
-  const unsigned gx = nblocks((size_t)op.nblk * 16, 256);
-  k_dslash<double, double2, __half2><<<gx * nb, 256, 0, s>>>(op, in, ins, out, fs, (int)gx, nb);
-  DD_LAUNCH_CHECK();
+  dslash_launch<double, double2, __half2>(op, in, ins, out, s, nb);
 }
 
 // ---------------------------------------------------------------------------
@@ -444,6 +696,18 @@ __device__ inline void inblock_hop(const C<T>* __restrict__ rs, int t, int loc, 
   oriented_hop<T, MU>([&](int c) { return rs[c * 256 + (t ^ bit)]; }, sg, u, acc);
 }
 
+// o = dag ? e^H : e for a stored 3x3 link
+template <typename S> __device__ inline void orient(const S (&e)[9], bool dag, S (&o)[9]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a)
+#pragma unroll
+    for (int b = 0; b < 3; ++b) {
+      S v = dag ? e[b * 3 + a] : e[a * 3 + b];
+      v.y = dag ? -v.y : v.y;
+      o[a * 3 + b] = v;
+    }
+}
+
 // The site's in-block links: loaded into registers once per pass for the
 // residual's in-block hops and the MR steps (FP32 and FP16 storage) or read
 // again at every use (FP64, where registers do not suffice).  The clover is read at every step: keeping it too (144 more
@@ -451,45 +715,34 @@ __device__ inline void inblock_hop(const C<T>* __restrict__ rs, int t, int loc, 
 // The link of in-block direction mu as the site applies it: the link
 // joining loc and loc ^ (1 << mu) belongs to the lower site, which applies
 // U; the upper site applies U^H (the transposed entries, conjugated).
-template <typename T, typename S>
-__device__ inline void oriented_link(const S* __restrict__ U, int blk, int loc, int mu, C<T> (&u)[9]) {
-  const bool up = (loc >> mu) & 1;
-  const S* p = U + (long long)blk * 576 + mu * 144 + (loc & ~(1 << mu));
-#pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const C<T> v = ldc<T, S>(p[(up ? b * 3 + a : a * 3 + b) * 16]);
-      u[a * 3 + b] = up ? cconj(v) : v;
-    }
+template <int MU, typename S>
+__device__ inline void oriented_link(const S* __restrict__ U, int blk, int loc, S (&o)[9]) {
+  const bool up = (loc >> MU) & 1;
+  S e[9];
+  load_entries<9 * MU, 9>(U, blk, loc & ~(1 << MU), e);
+  orient(e, up, o);
 }
 
 template <typename T, typename S, bool KEEP> struct BlockOp {
   S ul[KEEP ? 4 : 1][9];
   __device__ void load(const FineOpView<T, S>& op, int blk, int loc, bool valid) {
     if constexpr (KEEP) {
-#pragma unroll
-      for (int mu = 0; mu < 4; ++mu) {
-        const bool up = (loc >> mu) & 1;
-        const S* p = op.U + (long long)blk * 576 + mu * 144 + (loc & ~(1 << mu));
-#pragma unroll
-        for (int a = 0; a < 3; ++a)
-#pragma unroll
-          for (int b = 0; b < 3; ++b) {
-            S v = p[(up ? b * 3 + a : a * 3 + b) * 16];
-            if (up) v.y = -v.y;
-            ul[mu][a * 3 + b] = v;
-          }
-      }
+      oriented_link<0, S>(op.U, blk, loc, ul[0]);
+      oriented_link<1, S>(op.U, blk, loc, ul[1]);
+      oriented_link<2, S>(op.U, blk, loc, ul[2]);
+      oriented_link<3, S>(op.U, blk, loc, ul[3]);
     }
   }
   // the link as this site applies it (U or U^H)
-  __device__ void link(const FineOpView<T, S>& op, int blk, int loc, int mu, C<T> (&u)[9]) const {
+  template <int MU> __device__ void link(const FineOpView<T, S>& op, int blk, int loc, C<T> (&u)[9]) const {
     if constexpr (KEEP) {
 #pragma unroll
-      for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(ul[mu][k]);
+      for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(ul[MU][k]);
     } else {
-      oriented_link<T, S>(op.U, blk, loc, mu, u);
+      S o[9];
+      oriented_link<MU, S>(op.U, blk, loc, o);
+#pragma unroll
+      for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(o[k]);
     }
   }
   __device__ void clover(const FineOpView<T, S>& op, int blk, int loc, const C<T> v[12], C<T> out[12]) const {
@@ -498,21 +751,27 @@ template <typename T, typename S, bool KEEP> struct BlockOp {
 };
 
 // Whether a colour pass keeps each site's clover in LDS (one private slot
-// per thread, [36][256] entries of the stored type) for its MR steps instead
+// per thread, nine chunks) for its MR steps instead
 // of reading it from memory at every step: for FP16 storage the slots take
 // 36 KiB of a workgroup's LDS, which leaves the kernel's occupancy (set by
 // its registers) unchanged; in FP32 they would take 72 KiB and halve it.
 template <typename S> struct ClLds : std::false_type {};
 template <> struct ClLds<__half2> : std::true_type {};
 
-// Completes the arithmetic that produces acc before the statements that
-// follow (empty asm statements that read and write it), so that the next
-// direction's loads are not all issued ahead of it: hoisting the eight hops'
-// loads would need more registers than the colour pass can hold at two
-// wavefronts per SIMD.
-template <typename T> __device__ inline void pin12(C<T> (&acc)[12]) {
+// out = A v from a site's clover chunks in LDS (slot t of each)
+template <typename T, typename S>
+__device__ inline void clover_lds(const OpChunk<S>* cl, int t, const C<T> v[12], C<T> out[12]) {
+  constexpr int N = OpChunk<S>::N;
 #pragma unroll
-  for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[c].x), "+v"(acc[c].y));
+  for (int h = 0; h < 2; ++h) {
+    constexpr int NQ = (18 + N - 1) / N;
+    const int q0 = 18 * h / N;
+    OpChunk<S> c[NQ];
+#pragma unroll
+    for (int q = 0; q < NQ; ++q) c[q] = cl[(q0 + q) * 256 + t];
+    clover_block<T>(0, [&](int k) { return ldc<T, S>(c[(18 * h + k) / N - q0].v[(18 * h + k) % N]); }, v + 6 * h,
+                    out + 6 * h);
+  }
 }
 
 // The out-of-block hop of direction MU in the residual of a SAP block site:
@@ -529,14 +788,11 @@ __device__ inline void sap_outer_hop(const FineOpView<T, S>& op, const V* __rest
   const int nbb = up ? nb8.v[2 * MU] : nb8.v[2 * MU + 1];
   C<T> psi[12], u[9];
   load_site<T, V>(in, ins, nbb, loc ^ bit, psi);
-  const S* p = op.U + (long long)(up ? blk : nbb) * 576 + MU * 144 + (up ? loc : loc ^ bit);
+  S e[9], o[9];
+  load_entries<9 * MU, 9>(op.U, up ? blk : nbb, up ? loc : loc ^ bit, e);
+  orient(e, !up, o);
 #pragma unroll
-  for (int a = 0; a < 3; ++a)
-#pragma unroll
-    for (int b = 0; b < 3; ++b) {
-      const C<T> v = ldc<T, S>(p[(up ? a * 3 + b : b * 3 + a) * 16]);
-      u[a * 3 + b] = up ? v : cconj(v);
-    }
+  for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(o[k]);
   oriented_hop<T, MU>([&](int c) { return psi[c]; }, up ? T(1) : T(-1), u, acc);
 }
 
@@ -549,7 +805,7 @@ __device__ inline void sap_hops_mu(const FineOpView<T, S>& op, const V* __restri
                                    C<T> (&acc)[12]) {
   sap_outer_hop<T, S, V, MU>(op, in, ins, blk, loc, nb8, acc);
   C<T> u[9];
-  bop.link(op, blk, loc, MU, u);
+  bop.template link<MU>(op, blk, loc, u);
   inblock_hop<T, S, MU>(rs, t, loc, u, acc);
   pin12<T>(acc);
 }
@@ -568,15 +824,19 @@ __device__ inline void decode_kept(const V (&raw)[12], float m, C<T> v[12]) {
 }
 
 // one workgroup per (chunk of 16 blocks, field of the batch), gx chunks;
-// b and z in spinor storage V (bs, zs: their site scales for FP16)
-template <typename T, typename S, typename V>
+// b and z in spinor storage V (bs, zs: their site scales for FP16).  What is
+// read once in a pass (b) goes past the caches, and with NT (op_streams) the
+// result and the clover that is kept in LDS too: one field on 32^3x64 with
+// FP16 operators 2334 -> 2257 us for five sweeps, in FP32 3579 -> 3481 us (a
+// batch's z is found again in the last-level cache: 1469 -> 1553 us if not).
+template <typename T, typename S, typename V, bool NT>
 __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const int* __restrict__ cblk,
                                                     int ncb, int mr_iters, const V* __restrict__ b,
                                                     const float* __restrict__ bs, V* __restrict__ z,
                                                     float* __restrict__ zs, int nb, long long fs, int gx) {
   __shared__ C<T> rs[12 * 256];
   constexpr bool CL = ClLds<S>::value;
-  __shared__ S cl[CL ? 36 * 256 : 1];
+  __shared__ OpChunk<S> cl[CL ? 9 * 256 : 1];
   const int t = threadIdx.x;
   int xw, rw;
   xcd_slab_rhs(blockIdx.x, gx, nb, xw, rw);
@@ -597,9 +857,8 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
     C<T> rho[12], x[12];
     if constexpr (CL) {
       // the site's clover into its private LDS slot (read once per pass)
-      const S* pa = op.A + (long long)blk * 576 + loc;
 #pragma unroll
-      for (int e = 0; e < 36; ++e) cl[e * 256 + t] = pa[e * 16];
+      for (int q = 0; q < 9; ++q) cl[q * 256 + t] = NT ? load_chunk_nt<S>(op.A, blk, loc, q) : load_chunk<S>(op.A, blk, loc, q);
     }
     // the block's z in LDS: in-block neighbours and the site itself come
     // from there, the other neighbours from memory.  In FP32 arithmetic the
@@ -640,10 +899,10 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
       sap_hops_mu<T, S, V, 3>(op, z, zs, rs, t, blk, loc, nb8, bop, acc);
 #pragma unroll
       for (int c = 0; c < 12; ++c) zz[c] = rs[c * 256 + t];
-      if constexpr (CL) clover_mul<T>([&](int e) { return ldc<T, S>(cl[e * 256 + t]); }, zz, dz);
+      if constexpr (CL) clover_lds<T, S>(cl, t, zz, dz);
       else clover_apply<T, S>(op.A, blk, loc, zz, dz);
       C<T> bb[12];
-      load_site<T, V>(b, bs, blk, loc, bb);
+      load_site<T, V, true>(b, bs, blk, loc, bb);
 #pragma unroll
       for (int c = 0; c < 12; ++c) {
         rho[c].x = bb[c].x - dz[c].x + T(0.5) * acc[c].x;
@@ -666,16 +925,16 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
       for (int c = 0; c < 12; ++c) acc[c] = czero<T>();
       {
         C<T> u[9];
-        bop.link(op, blk, loc, 0, u);
+        bop.template link<0>(op, blk, loc, u);
         inblock_hop<T, S, 0>(rs, t, loc, u, acc);
-        bop.link(op, blk, loc, 1, u);
+        bop.template link<1>(op, blk, loc, u);
         inblock_hop<T, S, 1>(rs, t, loc, u, acc);
-        bop.link(op, blk, loc, 2, u);
+        bop.template link<2>(op, blk, loc, u);
         inblock_hop<T, S, 2>(rs, t, loc, u, acc);
-        bop.link(op, blk, loc, 3, u);
+        bop.template link<3>(op, blk, loc, u);
         inblock_hop<T, S, 3>(rs, t, loc, u, acc);
       }
-      if constexpr (CL) clover_mul<T>([&](int e) { return ldc<T, S>(cl[e * 256 + t]); }, rho, q);
+      if constexpr (CL) clover_lds<T, S>(cl, t, rho, q);
       else bop.clover(op, blk, loc, rho, q);
       T qr_re = 0, qr_im = 0, qq = 0;
 #pragma unroll
@@ -708,7 +967,7 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
       else load_site<T, V>(z, zs, blk, loc, zz);
 #pragma unroll
       for (int c = 0; c < 12; ++c) zz[c] = cadd(zz[c], x[c]);
-      store_site<T, V>(z, zs, blk, loc, zz);
+      store_site<T, V, NT>(z, zs, blk, loc, zz);
     }
   }
 }
@@ -720,8 +979,8 @@ void sap_colour(const FineOpView<T, S>& op, const int* colour_blocks, int colour
   const int ncb = op.nblk / 2;
   const long long fs = (long long)op.nblk * 192;
   const unsigned gx = nblocks(ncb, 16);
-  k_sap_colour<T, S, C<T>><<<gx * nb, 256, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, nullptr,
-                                                   z, nullptr, nb, fs, (int)gx);
+  const auto k = op_streams<S>(op.nblk, nb) ? k_sap_colour<T, S, C<T>, true> : k_sap_colour<T, S, C<T>, false>;
+  k<<<gx * nb, 256, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, nullptr, z, nullptr, nb, fs, (int)gx);
   DD_LAUNCH_CHECK();
 }
 
@@ -730,8 +989,9 @@ void sap_colour_hs(const FineOpView<float, __half2>& op, const int* colour_block
   const int ncb = op.nblk / 2;
   const long long fs = (long long)op.nblk * 192;
   const unsigned gx = nblocks(ncb, 16);
-  k_sap_colour<float, __half2, __half2><<<gx * nb, 256, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters,
-                                                                b, bs, z, zs, nb, fs, (int)gx);
+  const auto k = op_streams<__half2>(op.nblk, nb) ? k_sap_colour<float, __half2, __half2, true>
+                                                  : k_sap_colour<float, __half2, __half2, false>;
+  k<<<gx * nb, 256, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, bs, z, zs, nb, fs, (int)gx);
   DD_LAUNCH_CHECK();
 }
 
@@ -739,7 +999,6 @@ void sap_colour_hs(const FineOpView<float, __half2>& op, const int* colour_block
 #define DD_INST(T)                                                                              \
   template void fine_to_native<T>(const FineGeom&, const double2*, C<T>*, int, hipStream_t);   \
   template void fine_from_native<T>(const FineGeom&, const C<T>*, double2*, int, hipStream_t); \
-  template void links_to_native<T>(const FineGeom&, const double2*, C<T>*, hipStream_t);       \
   template void dslash<T, C<T>>(const FineOpView<T, C<T>>&, const C<T>*, C<T>*, hipStream_t, int); \
   template void sap_colour<T, C<T>>(const FineOpView<T, C<T>>&, const int*, int, int, const C<T>*, \
                                     C<T>*, hipStream_t, int);
@@ -750,12 +1009,6 @@ template void dslash<float, __half2>(const FineOpView<float, __half2>&, const fl
                                     int);
 template void sap_colour<float, __half2>(const FineOpView<float, __half2>&, const int*, int, int, const float2*,
                                          float2*, hipStream_t, int);
-
-__global__ void k_to_half(const double2* __restrict__ in, __half2* __restrict__ out, long long n) {
-  for (long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x; i < n;
-       i += (long long)gridDim.x * blockDim.x)
-    out[i] = __floats2half2_rn((float)in[i].x, (float)in[i].y);
-}
 
 __global__ void k_gamma5(const double2* in, double2* out, long long n) {
   long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
@@ -773,14 +1026,6 @@ void gamma5(const FineGeom& g, const double2* in, double2* out, int nb, hipStrea
   if (gr > 8192) gr = 8192;
   if (gr < 1) gr = 1;
   k_gamma5<<<(unsigned)gr, 256, 0, s>>>(in, out, n);
-  DD_LAUNCH_CHECK();
-}
-
-void to_half(const double2* in, __half2* out, long long n, hipStream_t s) {
-  long long g = (n + 255) / 256;
-  if (g > 4096) g = 4096;
-  if (g < 1) g = 1;
-  k_to_half<<<(unsigned)g, 256, 0, s>>>(in, out, n);
   DD_LAUNCH_CHECK();
 }
 

@@ -70,26 +70,58 @@ __device__ inline int xcd_slab_index(int bid, int nwg) {
   return (bid & 7) * (nwg >> 3) + (bid >> 3);
 }
 // The same for a batch of nb fields over a one-dimensional grid of gx * nb
-// workgroups: each XCD takes one slab of blocks and runs the nb fields of a
-// block chunk back to back, so the operator data of the chunk is fetched
-// into that XCD's L2 once for all of them.  Sets the workgroup's block-chunk
-// index x and field r.
+// workgroups: each XCD takes one slab of blocks and goes through it once per
+// group of XCD_FIELDS fields, running the fields of a group back to back on
+// each block chunk.  The operator data of a chunk is then fetched into that
+// XCD's L2 once per group, while the spinors of few enough fields pass through
+// it between one chunk and its neighbours for the chunks' faces to be still
+// there.  12 fields on 16^3x32, FP32, stencil in us for groups of 1, 2, 3, 4, 6,
+// 12: 258, 183, 174, 168, 166, 166 (inputs in the last-level cache; else 3: 209,
+// 4: 208, 6: 209, 12: 216); five FP32 SAP sweeps 2157, 1652, 1586, 1554, 1464, 1564.  Sets the workgroup's block-chunk index x and field r.
+constexpr int XCD_FIELDS = 6;
 __device__ inline void xcd_slab_rhs(int bid, int gx, int nb, int& x, int& r) {
   if (gx % 8 != 0) {
     x = bid % gx;
     r = bid / gx;
     return;
   }
-  const int k = bid >> 3;
-  x = (bid & 7) * (gx >> 3) + k / nb;
-  r = k % nb;
+  const int k = bid >> 3, slab = gx >> 3;
+  const int g = k / (slab * XCD_FIELDS), rem = k - g * slab * XCD_FIELDS, gs = min(XCD_FIELDS, nb - g * XCD_FIELDS);
+  x = (bid & 7) * slab + rem / gs;
+  r = g * XCD_FIELDS + rem % gs;
 }
 
-template <typename T, typename S = C<T>>
+// complex stores and loads of data that is not used again before it has left
+// the caches anyway
+__device__ inline void store_nt(float2* p, float2 v) {
+  typedef float v2 __attribute__((ext_vector_type(2)));
+  __builtin_nontemporal_store(__builtin_bit_cast(v2, v), reinterpret_cast<v2*>(p));
+}
+__device__ inline void store_nt(double2* p, double2 v) {
+  typedef double v2 __attribute__((ext_vector_type(2)));
+  __builtin_nontemporal_store(__builtin_bit_cast(v2, v), reinterpret_cast<v2*>(p));
+}
+
+__device__ inline void store_nt(__half2* p, __half2 v) {
+  __builtin_nontemporal_store(__builtin_bit_cast(float, v), reinterpret_cast<float*>(p));
+}
+__device__ inline float2 load_nt(const float2* p) {
+  typedef float v2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(float2, __builtin_nontemporal_load(reinterpret_cast<const v2*>(p)));
+}
+__device__ inline double2 load_nt(const double2* p) {
+  typedef double v2 __attribute__((ext_vector_type(2)));
+  return __builtin_bit_cast(double2, __builtin_nontemporal_load(reinterpret_cast<const v2*>(p)));
+}
+__device__ inline __half2 load_nt(const __half2* p) {
+  return __builtin_bit_cast(__half2, __builtin_nontemporal_load(reinterpret_cast<const float*>(p)));
+}
+
+template <typename T, typename S = C<T>, bool NT = false>
 __device__ inline void load_spinor(const S* __restrict__ f, int blk, int loc, C<T> v[12]) {
   const S* p = f + (long long)blk * 192 + loc;
 #pragma unroll
-  for (int c = 0; c < 12; ++c) v[c] = ldc<T, S>(p[c * 16]);
+  for (int c = 0; c < 12; ++c) v[c] = ldc<T, S>(NT ? load_nt(p + c * 16) : p[c * 16]);
 }
 // A fine spinor field of storage V: complex numbers of the arithmetic
 // precision (V = C<T>), or FP16 (V = __half2), each site's 12 components
@@ -97,10 +129,10 @@ __device__ inline void load_spinor(const S* __restrict__ f, int blk, int loc, C<
 // ([field][nblk * 16], native site order) next to them.  load_site /
 // store_site read and write one site in either form; the scale pointer is
 // not used for V = C<T>.
-template <typename T, typename V>
+template <typename T, typename V, bool NT = false>
 __device__ inline void load_site(const V* __restrict__ f, const float* __restrict__ sc, int blk, int loc,
                                  C<T> v[12]) {
-  load_spinor<T, V>(f, blk, loc, v);
+  load_spinor<T, V, NT>(f, blk, loc, v);
   if constexpr (std::is_same<V, __half2>::value) {
     const T m = sc[(long long)blk * 16 + loc];
 #pragma unroll
@@ -110,7 +142,7 @@ __device__ inline void load_site(const V* __restrict__ f, const float* __restric
     }
   }
 }
-template <typename T, typename V>
+template <typename T, typename V, bool NT = false>
 __device__ inline void store_site(V* __restrict__ f, float* __restrict__ sc, int blk, int loc, const C<T> v[12]) {
   V* p = f + (long long)blk * 192 + loc;
   if constexpr (std::is_same<V, __half2>::value) {
@@ -120,18 +152,61 @@ __device__ inline void store_site(V* __restrict__ f, float* __restrict__ sc, int
     const float inv = m > 0.f ? 1.f / m : 0.f;
     sc[(long long)blk * 16 + loc] = m;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) p[c * 16] = __floats2half2_rn((float)v[c].x * inv, (float)v[c].y * inv);
+    for (int c = 0; c < 12; ++c) {
+      const __half2 h = __floats2half2_rn((float)v[c].x * inv, (float)v[c].y * inv);
+      if constexpr (NT) store_nt(p + c * 16, h);
+      else p[c * 16] = h;
+    }
   } else {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) p[c * 16] = v[c];
+    for (int c = 0; c < 12; ++c) {
+      if constexpr (NT) store_nt(p + c * 16, v[c]);
+      else p[c * 16] = v[c];
+    }
   }
 }
 
-template <typename T, typename S = C<T>>
-__device__ inline void load_link(const S* __restrict__ U, int blk, int loc, int mu, C<T> u[9]) {
-  const S* p = U + (long long)blk * 576 + mu * 144 + loc;
+// The operator data of a site, 36 link entries (direction mu at 9 mu) or 36
+// clover entries, is stored in 16-byte chunks of N consecutive entries (see
+// fine.h), so that a load of operator data is 16 bytes per lane: the stencil
+// kernels issue so many loads that their number counts (216 per site and field
+// with one entry each; five FP32 SAP sweeps on 12 fields of 16^3x32 1730 ->
+// 1564 us, five on FP16 operators on 32^3x64 2471 -> 2334 us).
+template <typename S> struct alignas(16) OpChunk {
+  static constexpr int N = 16 / (int)sizeof(S);
+  S v[N];
+};
+template <typename S>
+__device__ inline OpChunk<S> load_chunk(const S* __restrict__ p, int blk, int loc, int q) {
+  return *reinterpret_cast<const OpChunk<S>*>(p + (long long)blk * 576 + (q * 16 + loc) * OpChunk<S>::N);
+}
+// (for data read once: not kept in the caches at the expense of what is reused)
+typedef float f32x4v __attribute__((ext_vector_type(4)));
+template <typename S>
+__device__ inline OpChunk<S> load_chunk_nt(const S* __restrict__ p, int blk, int loc, int q) {
+  const f32x4v v = __builtin_nontemporal_load(
+      reinterpret_cast<const f32x4v*>(p + (long long)blk * 576 + (q * 16 + loc) * OpChunk<S>::N));
+  return __builtin_bit_cast(OpChunk<S>, v);
+}
+// entries [E0, E0 + NE) of a site's operator data, as stored
+template <int E0, int NE, bool NT = false, typename S>
+__device__ inline void load_entries(const S* __restrict__ p, int blk, int loc, S (&e)[NE]) {
+  constexpr int N = OpChunk<S>::N, Q0 = E0 / N, Q1 = (E0 + NE - 1) / N;
 #pragma unroll
-  for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(p[k * 16]);
+  for (int q = Q0; q <= Q1; ++q) {
+    const OpChunk<S> c = NT ? load_chunk_nt<S>(p, blk, loc, q) : load_chunk<S>(p, blk, loc, q);
+#pragma unroll
+    for (int k = 0; k < N; ++k)
+      if (q * N + k >= E0 && q * N + k < E0 + NE) e[q * N + k - E0] = c.v[k];
+  }
+}
+
+template <typename T, int MU, typename S = C<T>>
+__device__ inline void load_link(const S* __restrict__ U, int blk, int loc, C<T> u[9]) {
+  S e[9];
+  load_entries<9 * MU, 9>(U, blk, loc, e);
+#pragma unroll
+  for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(e[k]);
 }
 
 // out = A(x) v for the packed clover of one site (both chiralities); get(e)
@@ -164,11 +239,19 @@ __device__ inline void clover_mul(G&& get, const C<T> v[12], C<T> out[12]) {
   for (int h = 0; h < 2; ++h) clover_block<T>(h, get, v + 6 * h, out + 6 * h);
 }
 
-template <typename T, typename S = C<T>>
+template <typename T, typename S = C<T>, bool NT = false>
 __device__ inline void clover_apply(const S* __restrict__ A, int blk, int loc, const C<T> v[12],
                                     C<T> out[12]) {
-  const S* p = A + (long long)blk * 576 + loc;
-  clover_mul<T>([&](int e) { return ldc<T, S>(p[e * 16]); }, v, out);
+  {
+    S e[18];
+    load_entries<0, 18, NT>(A, blk, loc, e);
+    clover_block<T>(0, [&](int k) { return ldc<T, S>(e[k]); }, v, out);
+  }
+  {
+    S e[18];
+    load_entries<18, 18, NT>(A, blk, loc, e);
+    clover_block<T>(0, [&](int k) { return ldc<T, S>(e[k]); }, v + 6, out + 6);
+  }
 }
 
 }  // namespace ddamg

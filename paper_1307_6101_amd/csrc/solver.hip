@@ -127,10 +127,10 @@ Context* create_context(const ddamg_lattice* lat, const double2* links, hipStrea
   const WorkspaceScope scope(c->ws.get());
   context_layout(*c, lat, half, nrhs_max, s);
   const FineGeom& g = c->g;
-  links_to_native<double>(g, links, c->U64.p, s);
-  links_to_native<float>(g, links, c->U32.p, s);
+  links_to_native(g, links, c->U64.p, s);
+  op_store<float2>(g, c->U64.p, c->U32.p, s);
   clover_build(g, links, lat->m0, lat->csw, c->A64.p, s);
-  vcopy<double, float>(c->A64.p, c->A32.p, (long long)g.V * 36, s);
+  op_store<float2>(g, c->A64.p, c->A32.p, s);
   if (c->U16.p) c->make_half(s);
   DD_CHECK_HIP(hipStreamSynchronize(s));
   return c.release();
@@ -144,8 +144,8 @@ void Context::make_half(hipStream_t s) {
     U16.alloc((size_t)g.V * 36);
     A16.alloc((size_t)g.V * 36);
   }
-  to_half(U64.p, U16.p, (long long)g.V * 36, s);
-  to_half(A64.p, A16.p, (long long)g.V * 36, s);
+  op_store<__half2>(g, U64.p, U16.p, s);
+  op_store<__half2>(g, A64.p, A16.p, s);
   half_ready = true;
 }
 

@@ -778,7 +778,7 @@ __device__ inline void gal_hop(const FineOpView<double>& op, const double2* Pk, 
     h[a] = p[(s0 * 3 + a) * 16];
     h[3 + a] = p[(s1 * 3 + a) * 16];
   }
-  load_link<double>(op.U, blk, loc, MU, u);
+  load_link<double, MU>(op.U, blk, loc, u);
 #pragma unroll
   for (int a = 0; a < 6; ++a) h[a] = live ? cscale(h[a], -0.5) : czero<double>();
   const double2 one = make_double2(1.0, 0.0);

@@ -1,0 +1,49 @@
+"""The stencil on both sides of the line between the split kernel (four
+wavefronts per 64 sites, up to 64 tiles of 256 sites in a call) and one site
+per thread, on native and canonical fields, against the FP64 oracle; native
+and canonical calls agree bit for bit on either side.
+
+Tolerance: sums of some 100 products per component: 1e-13 in FP64 and 1e-5 in
+FP32; 4 u_16 for FP16 operator storage."""
+import numpy as np
+import pytest
+import torch
+
+import workloads as W
+from oracle.dirac import WilsonClover
+from tests.gpu_util import dev, empty, host, relerr, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def dd():
+    from paper_1307_6101_amd import ddamg
+    ddamg.load_library()
+    return ddamg
+
+
+# tiles: 1, 4, 64 (the last split), 65, 12 * 6 = 72 of an odd tile grid
+@pytest.mark.parametrize("dims,nrhs", [((4, 4, 4, 4), 1), ((4, 8, 4, 8), 1), ((8, 8, 8, 8), 4), ((4, 4, 4, 20), 13),
+                                       ((12, 4, 8, 8), 6)])
+def test_stencil_paths(dd, dims, nrhs):
+    say(f"stencil dims={dims} nrhs={nrhs}")
+    U = W.links(dims, 0.5, 31)
+    op = WilsonClover(U, -0.3, 1.0)
+    psi = W.gaussian_spinor(dims, 32, nrhs=nrhs)
+    ref = np.stack([op.apply(p) for p in psi])
+    ctx = dd.create(dims, -0.3, 1.0, dev(U))
+    x, V = dev(psi), int(np.prod(dims))
+    for prec, cdt, tol in ((dd.F64, torch.complex128, 1e-13), (dd.F32, torch.complex64, 1e-5),
+                           (dd.F16, torch.complex64, 4 * 2.0 ** -11)):
+        out = empty(psi.shape)
+        dd.apply_D(ctx, x, out, nrhs=nrhs, prec=prec)
+        assert max(relerr(host(out)[r], ref[r]) for r in range(nrhs)) <= tol
+        conv = dd.F64 if prec == dd.F64 else dd.F32
+        nat = torch.zeros((nrhs, V * 12), dtype=cdt, device="cuda")
+        dd.to_native(ctx, None, 0, x, nat, nrhs=nrhs, prec=conv)
+        nout = torch.zeros_like(nat)
+        dd.apply_D(ctx, nat, nout, nrhs=nrhs, prec=prec, layout=dd.NATIVE)
+        back = empty(psi.shape)
+        dd.from_native(ctx, None, 0, nout, back, nrhs=nrhs, prec=conv)
+        assert np.array_equal(host(back), host(out)), prec
