@@ -165,9 +165,11 @@ void encode_h(const FineGeom& g, const C<T>* in, __half2* half, float* scale, in
 template <typename T>
 void decode_h(const FineGeom& g, const __half2* half, const float* scale, C<T>* out, int nb, hipStream_t s);
 
-// out = Gamma5 in for nb native fine fields (spins 3 and 4, components
-// 6..11, change sign; in == out allowed)
-void gamma5(const FineGeom& g, const double2* in, double2* out, int nb, hipStream_t s);
-
+// out = D in, or with g5 out = D^H in = Gamma5 D Gamma5 in, for nb native FP64
+// fields, and the sums of |out|^2 over parts of each field in a fixed order
+// (partial [nb][dslash_norm_parts(nblk)])
+inline int dslash_norm_parts(int nblk) { return nblk / 16; }
+void dslash_norm(const FineOpView<double>& op, const double2* in, double2* out, bool g5, double* partial,
+                 hipStream_t s, int nb = 1);
 
 }  // namespace ddamg

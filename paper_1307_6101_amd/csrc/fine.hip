@@ -469,6 +469,59 @@ __global__ void __launch_bounds__(256) k_dslash(FineOpView<T, S> op, const V* __
   for (int c = 0; c < 12; ++c) store_nt(p + c * 16, o[c]);
 }
 
+// D, or with G5 its adjoint Gamma5 D Gamma5 (the signs of the lower spins
+// applied as they are loaded and stored), on native FP64 fields, and per
+// workgroup the sum of |out|^2 (partial[field * gx + chunk])
+struct NativeG5In : NativeIn<double, double2> {
+  __device__ inline void site(int blk, int loc, double2 v[12]) const {
+    NativeIn<double, double2>::site(blk, loc, v);
+#pragma unroll
+    for (int c = 6; c < 12; ++c) v[c] = make_double2(-v[c].x, -v[c].y);
+  }
+  template <int MU, bool FWD> __device__ inline void hop(int nb, int loc, double2 v[12]) const {
+    site(nb, loc ^ (1 << MU), v);
+  }
+};
+template <bool G5, bool NT>
+__global__ void __launch_bounds__(256) k_dslash_norm(FineOpView<double> op, const double2* __restrict__ in,
+                                                     double2* __restrict__ out, double* __restrict__ partial,
+                                                     long long fs, int gx, int nb) {
+  __shared__ double sums[4];
+  int x, r;
+  xcd_slab_rhs(blockIdx.x, gx, nb, x, r);
+  const int blk = x * 16 + (threadIdx.x >> 4), loc = threadIdx.x & 15;   // nblk is a multiple of 16
+  const long long off = (long long)r * fs;
+  double2 o[12];
+  using In = std::conditional_t<G5, NativeG5In, NativeIn<double, double2>>;
+  In f;
+  f.in = in + off;
+  f.ins = nullptr;
+  dslash_site<double, double2, NT>(op, f, blk, loc, o);
+  double2* p = out + off + (long long)blk * 192 + loc;
+  double s = 0.0;
+#pragma unroll
+  for (int c = 0; c < 12; ++c) {
+    s = rfma(o[c].x, o[c].x, s);
+    s = rfma(o[c].y, o[c].y, s);
+    p[c * 16] = G5 && c >= 6 ? make_double2(-o[c].x, -o[c].y) : o[c];
+  }
+  s = group_sum<64>(s);
+  if ((threadIdx.x & 63) == 0) sums[threadIdx.x >> 6] = s;
+  __syncthreads();
+  if (threadIdx.x == 0) partial[(long long)r * gx + x] = (sums[0] + sums[1]) + (sums[2] + sums[3]);
+}
+
+void dslash_norm(const FineOpView<double>& op, const double2* in, double2* out, bool g5, double* partial,
+                 hipStream_t s, int nb) {
+  const long long fs = (long long)op.nblk * 192;
+  const int gx = dslash_norm_parts(op.nblk);
+  const bool nt = op_streams<double2>(op.nblk, nb);
+  const auto k = g5 ? (nt ? k_dslash_norm<true, true> : k_dslash_norm<true, false>)
+                    : (nt ? k_dslash_norm<false, true> : k_dslash_norm<false, false>);
+  k<<<gx * nb, 256, 0, s>>>(op, in, out, partial, fs, gx, nb);
+  DD_LAUNCH_CHECK();
+}
+
 // The stencil on canonical complex128 fields, without native copies of them:
 // a site's spinor is 192 contiguous bytes to read, and the workgroup's 4^4
 // tile of results goes through LDS to be written in rows of four sites (768
@@ -1009,25 +1062,6 @@ template void dslash<float, __half2>(const FineOpView<float, __half2>&, const fl
                                     int);
 template void sap_colour<float, __half2>(const FineOpView<float, __half2>&, const int*, int, int, const float2*,
                                          float2*, hipStream_t, int);
-
-__global__ void k_gamma5(const double2* in, double2* out, long long n) {
-  long long i = blockIdx.x * (long long)blockDim.x + threadIdx.x;
-  for (; i < n; i += (long long)gridDim.x * blockDim.x) {
-    // native layout [block][component][16 sites]: component (i / 16) % 12
-    const int c = (int)((i >> 4) % 12);
-    const double2 v = in[i];
-    out[i] = c < 6 ? v : make_double2(-v.x, -v.y);
-  }
-}
-
-void gamma5(const FineGeom& g, const double2* in, double2* out, int nb, hipStream_t s) {
-  const long long n = (long long)g.nblk * 192 * nb;
-  long long gr = (n + 255) / 256;
-  if (gr > 8192) gr = 8192;
-  if (gr < 1) gr = 1;
-  k_gamma5<<<(unsigned)gr, 256, 0, s>>>(in, out, n);
-  DD_LAUNCH_CHECK();
-}
 
 // one thread per site and field: largest |re|, |im| of the 12 components,
 // the components divided by it rounded to FP16, and their decoded FP64 value
