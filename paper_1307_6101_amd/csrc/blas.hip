@@ -69,7 +69,8 @@ __device__ inline double wsum(double v) {
 
 template <typename T, int BS, int KK>
 __device__ inline void dots_body(const C<T>* __restrict__ V, long long stride, C<T>* __restrict__ w,
-                                 long long n, bool upd, bool store, const Coefs& c, double* __restrict__ dst) {
+                                 long long n, bool upd, bool store, const Coefs& c, double* __restrict__ dst,
+                                 int dstride) {
   constexpr int k = KK;
   __shared__ double lds[BS / 64][2 * (KMAX + 1)];
   double acc[2 * KK + 1];
@@ -147,7 +148,7 @@ __device__ inline void dots_body(const C<T>* __restrict__ V, long long stride, C
   for (int j = threadIdx.x; j < nv; j += blockDim.x) {
     double sj = 0;
     for (int q = 0; q < BS / 64; ++q) sj += lds[q][j];
-    dst[j] = sj;
+    dst[(long long)j * dstride] = sj;
   }
 }
 
@@ -299,7 +300,7 @@ __global__ void __launch_bounds__(BS) k_bdots_pass1(const BArg a, int upd, const
     for (int j = 0; j < KK; ++j) cc.c[j] = a.coef(r, j);
   }
   dots_body<T, BS, KK>(V + (long long)r * n, vstride, w + (long long)r * n, n, upd != 0, upd == 1, cc,
-                       partial + ((long long)r * g + blockIdx.x) * 2 * (KMAX + 1));
+                       partial + (long long)r * 2 * (KMAX + 1) * g + blockIdx.x, g);
 }
 
 template <typename T, int KK>
@@ -322,20 +323,17 @@ struct BDotsLaunch<T, KMAX + 1> {
                  double*) {}
 };
 
-// second pass per system: block r reduces the g partial rows of system r
-__global__ void __launch_bounds__(256) k_bdots_pass2(const double* __restrict__ partial, int g, int nv,
-                                                     double* __restrict__ out) {
-  __shared__ double lds[4][2 * (KMAX + 1)];
-  const int t = threadIdx.x, lane = t & 63, wave = t >> 6, r = blockIdx.x;
-  const double* pr = partial + (long long)r * g * 2 * (KMAX + 1);
-  for (int j = 0; j < nv; ++j) {
-    double v = 0.0;
-    for (int q = t; q < g; q += 256) v += pr[(long long)q * 2 * (KMAX + 1) + j];
-    const double sv = wsum(v);
-    if (lane == 0) lds[wave][j] = sv;
-  }
-  __syncthreads();
-  if (t < nv) out[(long long)r * 2 * (KMAX + 1) + t] = lds[0][t] + lds[1][t] + lds[2][t] + lds[3][t];
+// second pass: one wavefront per value (blockIdx.y) and system (blockIdx.x), its
+// g parts contiguous (2048 parts of 12 values: 21 us with one workgroup for
+// all of a system's values, 4 us so)
+__global__ void __launch_bounds__(64) k_bdots_pass2(const double* __restrict__ partial, int g, double* __restrict__ out) {
+  const int r = blockIdx.x, j = blockIdx.y;
+  const double* pr = partial + ((long long)r * 2 * (KMAX + 1) + j) * g;
+  double v = 0.0;
+#pragma unroll 8
+  for (int q = threadIdx.x; q < g; q += 64) v += pr[q];
+  v = wsum(v);
+  if (threadIdx.x == 0) out[(long long)r * 2 * (KMAX + 1) + j] = v;
 }
 
 template <typename T>
@@ -355,7 +353,7 @@ void Reducer::bdots(const BArg* a, const C<T>* V, long long vstride, int k, C<T>
                         w, n, g == 1 ? out : partial_.p);
   DD_LAUNCH_CHECK();
   if (g > 1) {
-    k_bdots_pass2<<<nb, 256, 0, s>>>(partial_.p, (int)g, 2 * (k + 1), out);
+    k_bdots_pass2<<<dim3(nb, 2 * (k + 1)), 64, 0, s>>>(partial_.p, (int)g, out);
     DD_LAUNCH_CHECK();
   }
 }

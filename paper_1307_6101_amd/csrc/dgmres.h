@@ -32,8 +32,9 @@ struct DevGmres {
   double2* coef = nullptr;       // [NBMAX][KMAX]
   double* scale = nullptr;       // [NBMAX]
   long long* iters = nullptr;    // [NBMAX] iterations, accumulated
-  int* flag = nullptr;           // device alias of a coherent host word: set by
-                                 // gm_begin / gm_step / gm_solve (see below)
+  int* flag = nullptr;           // device alias of coherent host words: [0] set by
+                                 // gm_begin / gm_step / gm_solve, [1 + r] by the
+                                 // fused kernels for system r (see below)
   BArg arg() const {
     BArg a;
     a.inl = 0;
@@ -62,5 +63,25 @@ void gm_step(const DevGmres& d, int j, int m, int nb, hipStream_t s);
 // end of a cycle: coef = y = R^-1 g of every active system (zero beyond its
 // last step); flag = some system needs another cycle
 void gm_solve(const DevGmres& d, int m, int nb, hipStream_t s);
+
+// The same steps with their vector work for short vectors (those that a
+// workgroup holds in LDS: gm_short), one workgroup per system and one launch
+// each; flag[1 + r] as flag[0] above, per system.  Fields n apart, basis
+// vectors vs apart.
+constexpr long long GM_LDS = 53248;
+template <typename T> inline bool gm_short(long long n) { return n * (long long)sizeof(C<T>) <= GM_LDS; }
+// the norm of r0, gm_begin, V_0 = scale r0
+template <typename T>
+void gm_start(const DevGmres& d, const C<T>* r0, C<T>* V, long long n, int m, int nb, double tol, int first,
+              hipStream_t s);
+// step j: both Gram-Schmidt passes of w against V_0..V_j, gm_step, and (j + 1 < m)
+// V_{j+1}
+template <typename T>
+void gm_arnoldi(const DevGmres& d, C<T>* V, long long vs, const C<T>* w, long long n, int j, int m, int nb,
+                hipStream_t s);
+// gm_solve and x = V y (first) or x += V y
+template <typename T>
+void gm_finish(const DevGmres& d, const C<T>* V, long long vs, C<T>* x, long long n, int m, int nb, bool first,
+               hipStream_t s);
 
 }  // namespace ddamg

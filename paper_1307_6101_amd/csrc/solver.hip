@@ -554,7 +554,7 @@ DevGmres Hierarchy::gm() {
     ++gen;
   }
   if (!gm_flag_host && !counting_only()) {
-    DD_CHECK_HIP(hipHostMalloc(&gm_flag_host, sizeof(int), hipHostMallocCoherent));
+    DD_CHECK_HIP(hipHostMalloc(&gm_flag_host, sizeof(int) * (1 + NBMAX), hipHostMallocCoherent));
     DD_CHECK_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&gm_flag_dev), gm_flag_host, 0));
   }
   DevGmres d;
@@ -589,7 +589,7 @@ DevGmres Hierarchy::gmo() {
     ++gen;
   }
   if (!go_flag_host && !counting_only()) {
-    DD_CHECK_HIP(hipHostMalloc(&go_flag_host, sizeof(int), hipHostMallocCoherent));
+    DD_CHECK_HIP(hipHostMalloc(&go_flag_host, sizeof(int) * (1 + NBMAX), hipHostMallocCoherent));
     DD_CHECK_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&go_flag_dev), go_flag_host, 0));
   }
   DevGmres d;
@@ -712,11 +712,17 @@ void Hierarchy::gmres_dev(int l, Op op, const C<T>* b, C<T>* x, int m, int cycle
   const BArg a = d.arg();
   C<T>* V = W.V.p;
   C<T>* w = W.w.p;
-  vzero<T>(x, vs, s);
+  // short vectors: one launch per step, its flags per system
+  const bool fused = gm_short<T>(n);
+  if (!fused) vzero<T>(x, vs, s);
   // the liveness flag, read after the stream has drained
   auto flag_set = [&]() {
     DD_CHECK_HIP(hipStreamSynchronize(s));
-    return *static_cast<volatile int*>(gm_flag_host) != 0;
+    const volatile int* f = gm_flag_host;
+    if (!fused) return f[0] != 0;
+    bool any = false;
+    for (int r = 0; r < nb; ++r) any = any || f[1 + r] != 0;
+    return any;
   };
   for (int c = 0; c < cycles; ++c) {
     // r = b (first cycle) or b - A x: its norm starts the cycle
@@ -727,19 +733,27 @@ void Hierarchy::gmres_dev(int l, Op op, const C<T>* b, C<T>* x, int m, int cycle
       vbmy<T>(b, w, vs, s);
       r0 = w;
     }
-    red->bdots<T>(nullptr, r0, 0, 0, const_cast<C<T>*>(r0), n, nb, s, d.res);
-    gm_begin(d, m, nb, tol, c == 0, s);
-    bscale<T>(a, r0, V, n, nb, s);
+    if (fused) {
+      gm_start<T>(d, r0, V, n, m, nb, tol, c == 0, s);
+    } else {
+      red->bdots<T>(nullptr, r0, 0, 0, const_cast<C<T>*>(r0), n, nb, s, d.res);
+      gm_begin(d, m, nb, tol, c == 0, s);
+      bscale<T>(a, r0, V, n, nb, s);
+    }
     int steps = 0, polls = 0;
     const int first_poll = std::max(poll, pred_steps);
     for (int j = 0; j < m; ++j) {
       op(V + (size_t)j * vs, w);
-      red->bdots<T>(nullptr, V, vs, j + 1, w, n, nb, s, d.res);
-      gm_cgs1(d, j, nb, s);
-      red->bdots<T>(&a, V, vs, j + 1, w, n, nb, s, d.res);
-      gm_step(d, j, m, nb, s);
       steps = j + 1;
-      if (j + 1 < m) blincomb<T, T>(a, j + 1, V, vs, w, n, nb, V + (size_t)(j + 1) * vs, s);
+      if (fused) {
+        gm_arnoldi<T>(d, V, vs, w, n, j, m, nb, s);
+      } else {
+        red->bdots<T>(nullptr, V, vs, j + 1, w, n, nb, s, d.res);
+        gm_cgs1(d, j, nb, s);
+        red->bdots<T>(&a, V, vs, j + 1, w, n, nb, s, d.res);
+        gm_step(d, j, m, nb, s);
+        if (j + 1 < m) blincomb<T, T>(a, j + 1, V, vs, w, n, nb, V + (size_t)(j + 1) * vs, s);
+      }
       if (poll > 0 && j + 1 < m && j + 1 >= first_poll) {
         ++polls;
         if (!flag_set()) break;
@@ -750,9 +764,13 @@ void Hierarchy::gmres_dev(int l, Op op, const C<T>* b, C<T>* x, int m, int cycle
       // every system done, else at the step where they were
       pred_steps = polls <= 1 ? std::max(1, steps - 1) : steps;
     }
-    gm_solve(d, m, nb, s);
-    // only the basis vectors written in this cycle
-    blincomb<T, T>(a, steps, V, vs, x, n, nb, nullptr, s);
+    if (fused) {
+      gm_finish<T>(d, V, vs, x, n, m, nb, c == 0, s);
+    } else {
+      gm_solve(d, m, nb, s);
+      // only the basis vectors written in this cycle
+      blincomb<T, T>(a, steps, V, vs, x, n, nb, nullptr, s);
+    }
   }
 }
 
