@@ -738,15 +738,17 @@ __device__ inline void oriented_hop(G&& get, T sg, const C<T> (&u)[9], C<T> acc[
     }
 }
 
+constexpr int SAP_WG = 64;
+
 // The in-block hop of direction MU, the neighbour's spinor in LDS (rs,
-// [12][256], the site at column t): forward for the lower site of the pair,
+// [12][SAP_WG], the site at column t): forward for the lower site of the pair,
 // backward for the upper one
 template <typename T, typename S, int MU>
 __device__ inline void inblock_hop(const C<T>* __restrict__ rs, int t, int loc, const C<T> (&u)[9],
                                    C<T> acc[12]) {
   constexpr int bit = 1 << MU;
   const T sg = (loc & bit) ? T(-1) : T(1);
-  oriented_hop<T, MU>([&](int c) { return rs[c * 256 + (t ^ bit)]; }, sg, u, acc);
+  oriented_hop<T, MU>([&](int c) { return rs[c * SAP_WG + (t ^ bit)]; }, sg, u, acc);
 }
 
 // o = dag ? e^H : e for a stored 3x3 link
@@ -821,7 +823,7 @@ __device__ inline void clover_lds(const OpChunk<S>* cl, int t, const C<T> v[12],
     const int q0 = 18 * h / N;
     OpChunk<S> c[NQ];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) c[q] = cl[(q0 + q) * 256 + t];
+    for (int q = 0; q < NQ; ++q) c[q] = cl[(q0 + q) * SAP_WG + t];
     clover_block<T>(0, [&](int k) { return ldc<T, S>(c[(18 * h + k) / N - q0].v[(18 * h + k) % N]); }, v + 6 * h,
                     out + 6 * h);
   }
@@ -883,13 +885,13 @@ __device__ inline void decode_kept(const V (&raw)[12], float m, C<T> v[12]) {
 // FP16 operators 2334 -> 2257 us for five sweeps, in FP32 3579 -> 3481 us (a
 // batch's z is found again in the last-level cache: 1469 -> 1553 us if not).
 template <typename T, typename S, typename V, bool NT>
-__global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const int* __restrict__ cblk,
+__global__ void __launch_bounds__(SAP_WG) k_sap_colour(FineOpView<T, S> op, const int* __restrict__ cblk,
                                                     int ncb, int mr_iters, const V* __restrict__ b,
                                                     const float* __restrict__ bs, V* __restrict__ z,
                                                     float* __restrict__ zs, int nb, long long fs, int gx) {
-  __shared__ C<T> rs[12 * 256];
+  __shared__ C<T> rs[12 * SAP_WG];
   constexpr bool CL = ClLds<S>::value;
-  __shared__ OpChunk<S> cl[CL ? 9 * 256 : 1];
+  __shared__ OpChunk<S> cl[CL ? 9 * SAP_WG : 1];
   const int t = threadIdx.x;
   int xw, rw;
   xcd_slab_rhs(blockIdx.x, gx, nb, xw, rw);
@@ -900,7 +902,7 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
     bs += (long long)rw * (fs / 12);
     zs += (long long)rw * (fs / 12);
   }
-  const int jb = xw * 16 + (t >> 4);
+  const int jb = xw * (SAP_WG / 16) + (t >> 4);
   const int loc = t & 15;
   const bool valid = jb < ncb;
   const int blk = valid ? cblk[jb] : 0;
@@ -911,7 +913,7 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
     if constexpr (CL) {
       // the site's clover into its private LDS slot (read once per pass)
 #pragma unroll
-      for (int q = 0; q < 9; ++q) cl[q * 256 + t] = NT ? load_chunk_nt<S>(op.A, blk, loc, q) : load_chunk<S>(op.A, blk, loc, q);
+      for (int q = 0; q < 9; ++q) cl[q * SAP_WG + t] = NT ? load_chunk_nt<S>(op.A, blk, loc, q) : load_chunk<S>(op.A, blk, loc, q);
     }
     // the block's z in LDS: in-block neighbours and the site itself come
     // from there, the other neighbours from memory.  In FP32 arithmetic the
@@ -936,7 +938,7 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
         }
       }
 #pragma unroll
-      for (int c = 0; c < 12; ++c) rs[c * 256 + t] = zz[c];
+      for (int c = 0; c < 12; ++c) rs[c * SAP_WG + t] = zz[c];
     }
     // the in-block links, for the residual's in-block hops and the MR steps
     bop.load(op, blk, loc, valid);
@@ -951,7 +953,7 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
       sap_hops_mu<T, S, V, 2>(op, z, zs, rs, t, blk, loc, nb8, bop, acc);
       sap_hops_mu<T, S, V, 3>(op, z, zs, rs, t, blk, loc, nb8, bop, acc);
 #pragma unroll
-      for (int c = 0; c < 12; ++c) zz[c] = rs[c * 256 + t];
+      for (int c = 0; c < 12; ++c) zz[c] = rs[c * SAP_WG + t];
       if constexpr (CL) clover_lds<T, S>(cl, t, zz, dz);
       else clover_apply<T, S>(op.A, blk, loc, zz, dz);
       C<T> bb[12];
@@ -971,7 +973,7 @@ __global__ void __launch_bounds__(256) k_sap_colour(FineOpView<T, S> op, const i
 
     for (int it = 0; it < mr_iters; ++it) {
 #pragma unroll
-      for (int c = 0; c < 12; ++c) rs[c * 256 + t] = rho[c];
+      for (int c = 0; c < 12; ++c) rs[c * SAP_WG + t] = rho[c];
       __syncthreads();
       C<T> q[12], acc[12];
 #pragma unroll
@@ -1031,9 +1033,9 @@ void sap_colour(const FineOpView<T, S>& op, const int* colour_blocks, int colour
                 const C<T>* b, C<T>* z, hipStream_t s, int nb) {
   const int ncb = op.nblk / 2;
   const long long fs = (long long)op.nblk * 192;
-  const unsigned gx = nblocks(ncb, 16);
+  const unsigned gx = nblocks(ncb, SAP_WG / 16);
   const auto k = op_streams<S>(op.nblk, nb) ? k_sap_colour<T, S, C<T>, true> : k_sap_colour<T, S, C<T>, false>;
-  k<<<gx * nb, 256, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, nullptr, z, nullptr, nb, fs, (int)gx);
+  k<<<gx * nb, SAP_WG, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, nullptr, z, nullptr, nb, fs, (int)gx);
   DD_LAUNCH_CHECK();
 }
 
@@ -1041,10 +1043,10 @@ void sap_colour_hs(const FineOpView<float, __half2>& op, const int* colour_block
                    const __half2* b, const float* bs, __half2* z, float* zs, hipStream_t s, int nb) {
   const int ncb = op.nblk / 2;
   const long long fs = (long long)op.nblk * 192;
-  const unsigned gx = nblocks(ncb, 16);
+  const unsigned gx = nblocks(ncb, SAP_WG / 16);
   const auto k = op_streams<__half2>(op.nblk, nb) ? k_sap_colour<float, __half2, __half2, true>
                                                   : k_sap_colour<float, __half2, __half2, false>;
-  k<<<gx * nb, 256, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, bs, z, zs, nb, fs, (int)gx);
+  k<<<gx * nb, SAP_WG, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, bs, z, zs, nb, fs, (int)gx);
   DD_LAUNCH_CHECK();
 }
 
