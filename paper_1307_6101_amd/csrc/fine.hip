@@ -694,335 +694,365 @@ void dslash_hs(const FineOpView<double>& op, const __half2* in, const float* ins
 }
 
 // ---------------------------------------------------------------------------
-// SAP colour pass.  One thread per site, 16 lanes per 2^4 block, 16 blocks
-// per workgroup; a batch of fields runs one field per workgroup with the
-// XCD-aware batch mapping.  r = b - D z with the full operator (the blocks'
-// z staged in LDS: the in-block neighbours come from there, the others from
-// memory), then mr_iters minimal residual steps on the Dirichlet block
-// operator D_i (self term + the four in-block hops, partner spinors
-// exchanged through LDS, block sums of the step sizes by DPP row moves),
-// z += x.  The four in-block links of a site are read once into registers,
-// in their stored precision and as the site applies them (U for the lower
-// site of a pair, U^H for the upper one), so that forward and backward
-// in-block hops run the same instructions; with FP16 storage the clover is
-// kept in LDS for the pass.
+// SAP colour pass.  Two lanes per site: lanes 0-15 of a 32-lane group take a 2^4
+// block's sites with p = 0, lanes 16-31 the same sites with p = 1; a wavefront
+// holds two blocks and is a workgroup by itself, so no wave waits for another.
+// A batch of fields runs one field per workgroup with the XCD-aware mapping.
+// r = b - D z with the full operator (the blocks' z staged in LDS: the in-block
+// neighbours come from there, the others from memory), then mr_iters minimal
+// residual steps on the Dirichlet block operator D_i (self term + the four
+// in-block hops, partner spinors exchanged through LDS, block sums of the step
+// sizes by DPP row moves), z += x.
+//
+// Lane p of a site holds its chirality p (six components) and that half of the
+// clover, and computes the hops of directions x, y (p = 0) or z, t (p = 1) for
+// all four spins; the partial sums of the other chirality then change lanes
+// (row swaps).  x and z both project with phases +-i, y and t with +-1, so both
+// lanes run the same instructions with signs of their own, and links are
+// loaded and turned (U for the lower site of a pair, U^H for the upper one)
+// once per site, not once per lane.  A lane keeps its links, and with FP16
+// storage its clover, in registers for the pass.
 // ---------------------------------------------------------------------------
-// The in-block hop of direction MU: forward (the lower site of the pair,
-// link U) or backward (the upper site, U^H), with the link passed as the site
-// applies it; the backward hop's projection phases are the forward ones times
-// -1 (sg), so every lane runs the same instructions.
-template <typename T, int MU, typename G>
-__device__ inline void oriented_hop(G&& get, T sg, const C<T> (&u)[9], C<T> acc[12]) {
-  using P = Proj<MU>;
-  constexpr int c0 = (4 - P::K0) & 3, c1 = (4 - P::K1) & 3;
-  C<T> h[6];
-#pragma unroll
-  for (int a = 0; a < 3; ++a) {
-    const C<T> p0 = get(a), p1 = get(3 + a);
-    const C<T> q0 = mul_ik<P::K0>(get(P::J0 * 3 + a));
-    const C<T> q1 = mul_ik<P::K1>(get(P::J1 * 3 + a));
-    h[a] = mk<T>(fma(sg, q0.x, p0.x), fma(sg, q0.y, p0.y));
-    h[3 + a] = mk<T>(fma(sg, q1.x, p1.x), fma(sg, q1.y, p1.y));
-  }
-#pragma unroll
-  for (int s = 0; s < 2; ++s)
-#pragma unroll
-    for (int a = 0; a < 3; ++a) {
-      C<T> v = cmul(u[a * 3], h[s * 3]);
-      cfma(v, u[a * 3 + 1], h[s * 3 + 1]);
-      cfma(v, u[a * 3 + 2], h[s * 3 + 2]);
-      acc[s * 3 + a] = cadd(acc[s * 3 + a], v);
-      const int j = s ? P::J1 : P::J0;
-      const C<T> w = s ? mul_ik<c1>(v) : mul_ik<c0>(v);
-      acc[j * 3 + a] = mk<T>(fma(sg, w.x, acc[j * 3 + a].x), fma(sg, w.y, acc[j * 3 + a].y));
-    }
-}
-
 constexpr int SAP_WG = 64;
 
-// The in-block hop of direction MU, the neighbour's spinor in LDS (rs,
-// [12][SAP_WG], the site at column t): forward for the lower site of the pair,
-// backward for the upper one
-template <typename T, typename S, int MU>
-__device__ inline void inblock_hop(const C<T>* __restrict__ rs, int t, int loc, const C<T> (&u)[9],
-                                   C<T> acc[12]) {
-  constexpr int bit = 1 << MU;
-  const T sg = (loc & bit) ? T(-1) : T(1);
-  oriented_hop<T, MU>([&](int c) { return rs[c * SAP_WG + (t ^ bit)]; }, sg, u, acc);
+// (a, b) of lane rows (16 lanes) r and r + 1, r even: a of row r + 1 changes
+// places with b of row r
+__device__ inline void row_swap(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ inline void row_swap(double& a, double& b) {
+  const auto lo = __builtin_amdgcn_permlane16_swap((unsigned)__double2loint(a), (unsigned)__double2loint(b), false, false);
+  const auto hi = __builtin_amdgcn_permlane16_swap((unsigned)__double2hiint(a), (unsigned)__double2hiint(b), false, false);
+  a = __hiloint2double((int)hi[0], (int)lo[0]);
+  b = __hiloint2double((int)hi[1], (int)lo[1]);
 }
 
-// o = dag ? e^H : e for a stored 3x3 link
+// the sum of v over the 32 lanes of a block, in each of them
+template <typename T> __device__ inline T block_sum(T v) {
+  T a = sum16<T>(v), b = a;
+  row_swap(a, b);
+  return a + b;
+}
+
+// NE operator entries of a site from E0 (lane p = 0) or E0 + 18 (p = 1)
+template <int E0, int NE, bool NT = false, typename S>
+__device__ inline void load_entries_pair(const S* __restrict__ d, int blk, int loc, int p, S (&e)[NE]) {
+  constexpr int N = OpChunk<S>::N, Q0 = E0 / N, Q1 = (E0 + 18) / N, O0 = E0 % N, O1 = (E0 + 18) % N;
+  constexpr int NQ = ((O0 > O1 ? O0 : O1) + NE + N - 1) / N;
+  static_assert(Q1 + NQ <= 36 / N, "past the site's entries");
+  S raw[NQ * N];
+#pragma unroll
+  for (int q = 0; q < NQ; ++q) {
+    const int i = (p ? Q1 : Q0) + q;
+    const OpChunk<S> c = NT ? load_chunk_nt<S>(d, blk, loc, i) : load_chunk<S>(d, blk, loc, i);
+#pragma unroll
+    for (int k = 0; k < N; ++k) raw[q * N + k] = c.v[k];
+  }
+#pragma unroll
+  for (int k = 0; k < NE; ++k) {
+    if constexpr (O0 == O1) e[k] = raw[O0 + k];
+    else e[k] = p ? raw[O1 + k] : raw[O0 + k];
+  }
+}
+
+// o = dag ? e^H : e for a stored 3x3 link: a select with a negated source for
+// each real and imaginary part; FP16 pairs in one select and a sign flip
 template <typename S> __device__ inline void orient(const S (&e)[9], bool dag, S (&o)[9]) {
 #pragma unroll
   for (int a = 0; a < 3; ++a)
 #pragma unroll
     for (int b = 0; b < 3; ++b) {
       S v = dag ? e[b * 3 + a] : e[a * 3 + b];
-      v.y = dag ? -v.y : v.y;
+      if constexpr (std::is_same<S, __half2>::value)
+        v = __builtin_bit_cast(S, __builtin_bit_cast(unsigned, v) ^ (dag ? 0x80000000u : 0u));
+      else
+        v.y = dag ? -v.y : v.y;
       o[a * 3 + b] = v;
     }
 }
 
-// The site's in-block links: loaded into registers once per pass for the
-// residual's in-block hops and the MR steps (FP32 and FP16 storage) or read
-// again at every use (FP64, where registers do not suffice).  The clover is read at every step: keeping it too (144 more
-// registers in FP32) leaves one wavefront per SIMD and was measured slower.
-// The link of in-block direction mu as the site applies it: the link
-// joining loc and loc ^ (1 << mu) belongs to the lower site, which applies
-// U; the upper site applies U^H (the transposed entries, conjugated).
-template <int MU, typename S>
-__device__ inline void oriented_link(const S* __restrict__ U, int blk, int loc, S (&o)[9]) {
-  const bool up = (loc >> MU) & 1;
-  S e[9];
-  load_entries<9 * MU, 9>(U, blk, loc & ~(1 << MU), e);
-  orient(e, up, o);
-}
+// The direction of step ST (0: x or z, 1: y or t) as a bit of the site index
+__device__ inline int pair_bit(int ST, int p) { return (p ? 4 : 1) << ST; }
 
-template <typename T, typename S, bool KEEP> struct BlockOp {
-  S ul[KEEP ? 4 : 1][9];
-  __device__ void load(const FineOpView<T, S>& op, int blk, int loc, bool valid) {
-    if constexpr (KEEP) {
-      oriented_link<0, S>(op.U, blk, loc, ul[0]);
-      oriented_link<1, S>(op.U, blk, loc, ul[1]);
-      oriented_link<2, S>(op.U, blk, loc, ul[2]);
-      oriented_link<3, S>(op.U, blk, loc, ul[3]);
-    }
-  }
-  // the link as this site applies it (U or U^H)
-  template <int MU> __device__ void link(const FineOpView<T, S>& op, int blk, int loc, C<T> (&u)[9]) const {
-    if constexpr (KEEP) {
-#pragma unroll
-      for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(ul[MU][k]);
-    } else {
-      S o[9];
-      oriented_link<MU, S>(op.U, blk, loc, o);
-#pragma unroll
-      for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(o[k]);
-    }
-  }
-  __device__ void clover(const FineOpView<T, S>& op, int blk, int loc, const C<T> v[12], C<T> out[12]) const {
-    clover_apply<T, S>(op.A, blk, loc, v, out);
-  }
+// A lane's partial sums of the hops: spins 2 and 3 (l1, l2), and the upper
+// spins they are projected with: u1 spin 1 - p, u2 spin p
+template <typename T> struct PairAcc {
+  C<T> u1[3], u2[3], l1[3], l2[3];
 };
 
-// Whether a colour pass keeps each site's clover in LDS (one private slot
-// per thread, nine chunks) for its MR steps instead
-// of reading it from memory at every step: for FP16 storage the slots take
-// 36 KiB of a workgroup's LDS, which leaves the kernel's occupancy (set by
-// its registers) unchanged; in FP32 they would take 72 KiB and halve it.
-template <typename S> struct ClLds : std::false_type {};
-template <> struct ClLds<__half2> : std::true_type {};
-
-// out = A v from a site's clover chunks in LDS (slot t of each)
-template <typename T, typename S>
-__device__ inline void clover_lds(const OpChunk<S>* cl, int t, const C<T> v[12], C<T> out[12]) {
-  constexpr int N = OpChunk<S>::N;
+// One projected hop of step ST; psi(i, a): i = 0, 1 the spins of u1, u2, i = 2,
+// 3 spins 2, 3.  sg = 1 (forward) or -1; the phases of the first pair are sg
+// i (x and z) or -sg (y and t), those of the second +-sg i, +-sg, - for p = 1.
+// The result is multiplied by m (the scale of FP16 spinors: applied in the
+// accumulation it costs nothing) and added to acc, or replaces it (FIRST).
+// MIX: links in FP16, which enter an fma unconverted, so there is no product
+// without one.
+template <typename T, int ST, bool FIRST, bool SCALED, bool MIX, typename G>
+__device__ inline void pair_hop(G&& psi, T sg, int p, const C<T> (&u)[9], T m, PairAcc<T>& acc) {
+  const T s1 = ST ? -sg : sg, s2 = p ? -sg : sg;
 #pragma unroll
-  for (int h = 0; h < 2; ++h) {
-    constexpr int NQ = (18 + N - 1) / N;
-    const int q0 = 18 * h / N;
-    OpChunk<S> c[NQ];
+  for (int i = 0; i < 2; ++i) {
+    const T s = i ? s2 : s1;
+    C<T>(&up)[3] = i ? acc.u2 : acc.u1;
+    C<T>(&lo)[3] = i ? acc.l2 : acc.l1;
+    C<T> h[3];
 #pragma unroll
-    for (int q = 0; q < NQ; ++q) c[q] = cl[(q0 + q) * SAP_WG + t];
-    clover_block<T>(0, [&](int k) { return ldc<T, S>(c[(18 * h + k) / N - q0].v[(18 * h + k) % N]); }, v + 6 * h,
-                    out + 6 * h);
-  }
-}
-
-// The out-of-block hop of direction MU in the residual of a SAP block site:
-// the neighbour outside the block is x+mu for the upper site of the pair
-// (link U_mu(x), the site's own) and x-mu for the lower one (link
-// U_mu(x-mu) of the neighbour block's site, applied as U^H).  The link is
-// loaded oriented, so both kinds of site run the same instructions.
-template <typename T, typename S, typename V, int MU>
-__device__ inline void sap_outer_hop(const FineOpView<T, S>& op, const V* __restrict__ in,
-                                     const float* __restrict__ ins, int blk, int loc, const Nbr8& nb8,
-                                     C<T> (&acc)[12]) {
-  constexpr int bit = 1 << MU;
-  const bool up = loc & bit;
-  const int nbb = up ? nb8.v[2 * MU] : nb8.v[2 * MU + 1];
-  C<T> psi[12], u[9];
-  load_site<T, V>(in, ins, nbb, loc ^ bit, psi);
-  S e[9], o[9];
-  load_entries<9 * MU, 9>(op.U, up ? blk : nbb, up ? loc : loc ^ bit, e);
-  orient(e, !up, o);
+    for (int a = 0; a < 3; ++a) {
+      const C<T> v = psi(i, a);
+      const C<T> w = ST ? psi(2 + i, a) : cmuli(psi(2 + i, a));
+      h[a] = mk<T>(fma(s, w.x, v.x), fma(s, w.y, v.y));
+    }
 #pragma unroll
-  for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(o[k]);
-  oriented_hop<T, MU>([&](int c) { return psi[c]; }, up ? T(1) : T(-1), u, acc);
-}
-
-// Both hops of direction MU in the residual: the out-of-block one from
-// memory, the in-block one from the staged z (rs) with the link the site
-// keeps for its MR steps
-template <typename T, typename S, typename V, int MU, typename B>
-__device__ inline void sap_hops_mu(const FineOpView<T, S>& op, const V* __restrict__ in, const float* __restrict__ ins,
-                                   const C<T>* rs, int t, int blk, int loc, const Nbr8& nb8, const B& bop,
-                                   C<T> (&acc)[12]) {
-  sap_outer_hop<T, S, V, MU>(op, in, ins, blk, loc, nb8, acc);
-  C<T> u[9];
-  bop.template link<MU>(op, blk, loc, u);
-  inblock_hop<T, S, MU>(rs, t, loc, u, acc);
-  pin12<T>(acc);
-}
-
-// a site's spinor from its stored components (and FP16 scale m), as load_site
-template <typename T, typename V>
-__device__ inline void decode_kept(const V (&raw)[12], float m, C<T> v[12]) {
-#pragma unroll
-  for (int c = 0; c < 12; ++c) {
-    v[c] = ldc<T, V>(raw[c]);
-    if constexpr (std::is_same<V, __half2>::value) {
-      v[c].x *= T(m);
-      v[c].y *= T(m);
+    for (int a = 0; a < 3; ++a) {
+      C<T> v;
+      if constexpr (MIX) {
+        v = czero<T>();
+        cfma(v, u[a * 3], h[0]);
+      } else {
+        v = cmul(u[a * 3], h[0]);
+      }
+      cfma(v, u[a * 3 + 1], h[1]);
+      cfma(v, u[a * 3 + 2], h[2]);
+      const C<T> w = ST ? v : cmulmi(v);
+      const T sm = SCALED ? s * m : s;
+      if constexpr (FIRST) {
+        up[a] = SCALED ? cscale(v, m) : v;
+        lo[a] = cscale(w, sm);
+      } else {
+        up[a] = SCALED ? mk<T>(fma(m, v.x, up[a].x), fma(m, v.y, up[a].y)) : cadd(up[a], v);
+        lo[a] = mk<T>(fma(sm, w.x, lo[a].x), fma(sm, w.y, lo[a].y));
+      }
     }
   }
 }
 
-// one workgroup per (chunk of 16 blocks, field of the batch), gx chunks;
-// b and z in spinor storage V (bs, zs: their site scales for FP16).  What is
-// read once in a pass (b) goes past the caches, and with NT (op_streams) the
-// result and the clover that is kept in LDS too: one field on 32^3x64 with
+// the sum of both lanes' partial sums, each lane its chirality
+template <typename T> __device__ inline void pair_total(PairAcc<T>& acc, int p, C<T> (&o)[6]) {
+#pragma unroll
+  for (int a = 0; a < 3; ++a) {
+    // afterwards (p = 0 | 1): u1 spin 1 | 3, l2 spin 0 | 3, u2 spin 0 | 2, l1 spin 1 | 2
+    row_swap(acc.u1[a].x, acc.l2[a].x);
+    row_swap(acc.u1[a].y, acc.l2[a].y);
+    row_swap(acc.u2[a].x, acc.l1[a].x);
+    row_swap(acc.u2[a].y, acc.l1[a].y);
+    o[a] = cadd(acc.u2[a], p ? acc.l1[a] : acc.l2[a]);
+    o[3 + a] = cadd(acc.u1[a], p ? acc.l2[a] : acc.l1[a]);
+  }
+}
+
+// the in-block hop of step ST from the components staged in LDS (rs: the block's
+// [12][16]) with the link as the site applies it
+template <typename T, int ST, bool FIRST, typename S>
+__device__ inline void pair_inblock(const C<T>* rs, int loc, int p, const S (&o)[9], PairAcc<T>& acc) {
+  const int bit = pair_bit(ST, p);
+  const C<T>* r = rs + (loc ^ bit);
+  C<T> u[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(o[k]);
+  const int f1 = p ? 0 : 48, f2 = p ? 48 : 0;
+  pair_hop<T, ST, FIRST, false, std::is_same<S, __half2>::value>(
+      [&](int i, int a) { return r[i >= 2 ? (3 * i + a) * 16 : (i ? f2 : f1) + a * 16]; },
+      (loc & bit) ? T(-1) : T(1), p, u, T(1), acc);
+}
+
+// The in-block link of step ST as the site applies it: the link joining loc and
+// loc ^ bit belongs to the lower site, which applies U; the upper site applies
+// U^H (the transposed entries, conjugated).
+template <int ST, typename S>
+__device__ inline void pair_link(const S* __restrict__ U, int blk, int loc, int p, S (&o)[9]) {
+  const int bit = pair_bit(ST, p);
+  S e[9];
+  load_entries_pair<9 * ST, 9>(U, blk, loc & ~bit, p, e);
+  orient(e, (loc & bit) != 0, o);
+}
+
+// The out-of-block hop of step ST in the residual of a block site: the
+// neighbour outside the block is x+mu for the upper site of the pair (link
+// U_mu(x), the site's own) and x-mu for the lower one (link U_mu(x-mu) of the
+// neighbour block's site, applied as U^H).
+template <typename T, typename S, typename V, int ST>
+__device__ inline void pair_outer(const FineOpView<T, S>& op, const V* __restrict__ in, const float* __restrict__ ins,
+                                  int blk, int loc, int p, int nbf, int nbb, PairAcc<T>& acc) {
+  const int bit = pair_bit(ST, p);
+  const bool up = loc & bit;
+  const int nb = up ? nbf : nbb;
+  const V* f = in + (long long)nb * 192 + (loc ^ bit);
+  const int f1 = p ? 0 : 48, f2 = p ? 48 : 0;
+  V raw[12];
+#pragma unroll
+  for (int i = 0; i < 4; ++i)
+#pragma unroll
+    for (int a = 0; a < 3; ++a) raw[3 * i + a] = f[i >= 2 ? (3 * i + a) * 16 : (i ? f2 : f1) + a * 16];
+  float m = 1.f;
+  if constexpr (std::is_same<V, __half2>::value) m = ins[(long long)nb * 16 + (loc ^ bit)];
+  S e[9], o[9];
+  load_entries_pair<9 * ST, 9>(op.U, up ? blk : nb, up ? loc : loc ^ bit, p, e);
+  orient(e, !up, o);
+  C<T> u[9];
+#pragma unroll
+  for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(o[k]);
+  pair_hop<T, ST, ST == 0, std::is_same<V, __half2>::value, std::is_same<S, __half2>::value>(
+      [&](int i, int a) { return ldc<T, V>(raw[3 * i + a]); }, up ? T(1) : T(-1), p, u, T(m), acc);
+}
+
+// Whether a colour pass keeps its clover entries in registers for the MR steps
+// (FP16 storage: 18 registers) or reads them again at every step
+template <typename S> struct ClKeep : std::false_type {};
+template <> struct ClKeep<__half2> : std::true_type {};
+
+// One workgroup per (two blocks, field of the batch), gx pairs of blocks;
+// b and z in spinor storage V (bs, zs: their site scales for FP16).
+//
+// Bound by its vector instructions on batches (about 2500 a lane, two lanes a
+// site, at three waves per SIMD; one lane a site: 4335 at two), by memory for
+// one field of a large lattice, by latency on a small one, where the two lanes
+// double the wavefronts.  Five
+// sweeps, one lane a site in workgroups of four wavefronts / of one / this:
+// 32^3x64 FP16 operators 2264 / 2128 / 1915 us; 16^3x32 x 12 FP32 fields 1496 /
+// 1410 / 1358; per pass, 12 FP16 fields of 24^3x48 682 / 666 / 667, one FP32
+// field of 16^3x32 24.5 / 22.9 / 19.5; FP64 (two sweeps, 5 fields) - / 650 / 543.
+// Held to three waves per SIMD in FP32 (two: FP16 12-field pass 718).
+//
+// What is read once in a pass (b) goes past the caches, and with NT (op_streams)
+// the result and the clover that is kept too: one field on 32^3x64 with
 // FP16 operators 2334 -> 2257 us for five sweeps, in FP32 3579 -> 3481 us (a
 // batch's z is found again in the last-level cache: 1469 -> 1553 us if not).
 template <typename T, typename S, typename V, bool NT>
-__global__ void __launch_bounds__(SAP_WG) k_sap_colour(FineOpView<T, S> op, const int* __restrict__ cblk,
-                                                    int ncb, int mr_iters, const V* __restrict__ b,
-                                                    const float* __restrict__ bs, V* __restrict__ z,
-                                                    float* __restrict__ zs, int nb, long long fs, int gx) {
-  __shared__ C<T> rs[12 * SAP_WG];
-  constexpr bool CL = ClLds<S>::value;
-  __shared__ OpChunk<S> cl[CL ? 9 * SAP_WG : 1];
-  const int t = threadIdx.x;
+__global__ void __launch_bounds__(SAP_WG, sizeof(T) == 8 ? 2 : 3)
+k_sap_colour(FineOpView<T, S> op, const int* __restrict__ cblk,
+             int mr_iters, const V* __restrict__ b, const float* __restrict__ bs, V* __restrict__ z,
+             float* __restrict__ zs, int nb, long long fs, int gx) {
+  __shared__ C<T> rsm[2 * 192];
+  constexpr bool HS = std::is_same<V, __half2>::value;
+  constexpr bool KEEP = !std::is_same<T, double>::value;
+  constexpr bool CK = ClKeep<S>::value;
+  const int t = threadIdx.x, loc = t & 15, p = (t >> 4) & 1;
   int xw, rw;
   xcd_slab_rhs(blockIdx.x, gx, nb, xw, rw);
   b += (long long)rw * fs;
   z += (long long)rw * fs;
-  constexpr bool HS = std::is_same<V, __half2>::value;
   if constexpr (HS) {
     bs += (long long)rw * (fs / 12);
     zs += (long long)rw * (fs / 12);
   }
-  const int jb = xw * (SAP_WG / 16) + (t >> 4);
-  const int loc = t & 15;
-  const bool valid = jb < ncb;
-  const int blk = valid ? cblk[jb] : 0;
-  constexpr bool KEEP = !std::is_same<T, double>::value;
-  BlockOp<T, S, KEEP> bop;
-  {
-    C<T> rho[12], x[12];
-    if constexpr (CL) {
-      // the site's clover into its private LDS slot (read once per pass)
-#pragma unroll
-      for (int q = 0; q < 9; ++q) cl[q * SAP_WG + t] = NT ? load_chunk_nt<S>(op.A, blk, loc, q) : load_chunk<S>(op.A, blk, loc, q);
-    }
-    // the block's z in LDS: in-block neighbours and the site itself come
-    // from there, the other neighbours from memory.  In FP32 arithmetic the
-    // site's z also stays in registers as stored (and its scale) for the
-    // final z += x
-    constexpr bool KZ = !std::is_same<T, double>::value;
-    V zkeep[KZ ? 12 : 1];
-    float zsk = 1.f;
-    {
-      C<T> zz[12];
-#pragma unroll
-      for (int c = 0; c < 12; ++c) zz[c] = czero<T>();
-      if (valid) {
-        if constexpr (KZ) {
-          const V* pz = z + (long long)blk * 192 + loc;
-#pragma unroll
-          for (int c = 0; c < 12; ++c) zkeep[c] = pz[c * 16];
-          if constexpr (HS) zsk = zs[(long long)blk * 16 + loc];
-          decode_kept<T, V>(zkeep, zsk, zz);
-        } else {
-          load_site<T, V>(z, zs, blk, loc, zz);
-        }
-      }
-#pragma unroll
-      for (int c = 0; c < 12; ++c) rs[c * SAP_WG + t] = zz[c];
-    }
-    // the in-block links, for the residual's in-block hops and the MR steps
-    bop.load(op, blk, loc, valid);
-    __syncthreads();
-    if (valid) {
-      const Nbr8 nb8 = load_nbr8(op.nbr, blk);
-      C<T> acc[12], zz[12], dz[12];
-#pragma unroll
-      for (int c = 0; c < 12; ++c) acc[c] = czero<T>();
-      sap_hops_mu<T, S, V, 0>(op, z, zs, rs, t, blk, loc, nb8, bop, acc);
-      sap_hops_mu<T, S, V, 1>(op, z, zs, rs, t, blk, loc, nb8, bop, acc);
-      sap_hops_mu<T, S, V, 2>(op, z, zs, rs, t, blk, loc, nb8, bop, acc);
-      sap_hops_mu<T, S, V, 3>(op, z, zs, rs, t, blk, loc, nb8, bop, acc);
-#pragma unroll
-      for (int c = 0; c < 12; ++c) zz[c] = rs[c * SAP_WG + t];
-      if constexpr (CL) clover_lds<T, S>(cl, t, zz, dz);
-      else clover_apply<T, S>(op.A, blk, loc, zz, dz);
-      C<T> bb[12];
-      load_site<T, V, true>(b, bs, blk, loc, bb);
-#pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        rho[c].x = bb[c].x - dz[c].x + T(0.5) * acc[c].x;
-        rho[c].y = bb[c].y - dz[c].y + T(0.5) * acc[c].y;
-      }
-    } else {
-#pragma unroll
-      for (int c = 0; c < 12; ++c) rho[c] = czero<T>();
-    }
-    __syncthreads();   // rs is rewritten by the first MR step
-#pragma unroll
-    for (int c = 0; c < 12; ++c) x[c] = czero<T>();
+  const int blk = cblk[xw * 2 + (t >> 5)];
+  C<T>* rs = rsm + (t >> 5) * 192;           // the block's components [12][16]
+  C<T>* own = rs + p * 96 + loc;             // the lane's: own[c * 16]
+  const long long so = (long long)blk * 192 + p * 96 + loc, sc = (long long)blk * 16 + loc;
 
-    for (int it = 0; it < mr_iters; ++it) {
+  V zkeep[6];
+  float zsk = 1.f, bsk = 1.f;
 #pragma unroll
-      for (int c = 0; c < 12; ++c) rs[c * SAP_WG + t] = rho[c];
-      __syncthreads();
-      C<T> q[12], acc[12];
+  for (int c = 0; c < 6; ++c) zkeep[c] = z[so + c * 16];
+  if constexpr (HS) zsk = zs[sc];
+  S ul[KEEP ? 2 : 1][9];
+  if constexpr (KEEP) {
+    pair_link<0>(op.U, blk, loc, p, ul[0]);
+    pair_link<1>(op.U, blk, loc, p, ul[1]);
+  }
+  S ce[18];
+  if constexpr (CK) load_entries_pair<0, 18, NT>(op.A, blk, loc, p, ce);
+  const int* nbr = op.nbr + (long long)blk * 8 + (p ? 4 : 0);
+  const int4 nb4 = *reinterpret_cast<const int4*>(nbr);
+  V braw[6];
 #pragma unroll
-      for (int c = 0; c < 12; ++c) acc[c] = czero<T>();
-      {
-        C<T> u[9];
-        bop.template link<0>(op, blk, loc, u);
-        inblock_hop<T, S, 0>(rs, t, loc, u, acc);
-        bop.template link<1>(op, blk, loc, u);
-        inblock_hop<T, S, 1>(rs, t, loc, u, acc);
-        bop.template link<2>(op, blk, loc, u);
-        inblock_hop<T, S, 2>(rs, t, loc, u, acc);
-        bop.template link<3>(op, blk, loc, u);
-        inblock_hop<T, S, 3>(rs, t, loc, u, acc);
-      }
-      if constexpr (CL) clover_lds<T, S>(cl, t, rho, q);
-      else bop.clover(op, blk, loc, rho, q);
-      T qr_re = 0, qr_im = 0, qq = 0;
+  for (int c = 0; c < 6; ++c) braw[c] = load_nt(b + so + c * 16);
+  if constexpr (HS) bsk = bs[sc];
+
+  auto decode = [&](V v, float m) {
+    C<T> w = ldc<T, V>(v);
+    if constexpr (HS) w = mk<T>(w.x * T(m), w.y * T(m));
+    return w;
+  };
+  // acc (+)= the in-block hops of what is staged; q = A (own) - 1/2 total
+  PairAcc<T> acc;
+  auto inblock = [&](auto first) {
+    constexpr bool F = decltype(first)::value;
+    if constexpr (!KEEP) pair_link<0>(op.U, blk, loc, p, ul[0]);
+    pair_inblock<T, 0, F>(rs, loc, p, ul[0], acc);
+    if constexpr (!KEEP) pair_link<1>(op.U, blk, loc, p, ul[0]);
+    pair_inblock<T, 1, false>(rs, loc, p, ul[KEEP ? 1 : 0], acc);
+  };
+  auto diag = [&](const C<T> (&v)[6], C<T> (&o)[6]) {
+    if constexpr (!CK) load_entries_pair<0, 18>(op.A, blk, loc, p, ce);
+    clover_block<T>(0, [&](int k) { return ldc<T, S>(ce[k]); }, v, o);
+    C<T> h[6];
+    pair_total<T>(acc, p, h);
 #pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        q[c].x = rfma(T(-0.5), acc[c].x, q[c].x);
-        q[c].y = rfma(T(-0.5), acc[c].y, q[c].y);
-        qr_re = rfma(q[c].x, rho[c].x, qr_re);
-        qr_re = rfma(q[c].y, rho[c].y, qr_re);
-        qr_im = rfma(q[c].x, rho[c].y, qr_im);
-        qr_im = rfma(-q[c].y, rho[c].x, qr_im);
-        qq = rfma(q[c].x, q[c].x, qq);
-        qq = rfma(q[c].y, q[c].y, qq);
-      }
-      qr_re = sum16<T>(qr_re);
-      qr_im = sum16<T>(qr_im);
-      qq = sum16<T>(qq);
-      const T iq = qq > T(0) ? T(1) / qq : T(0);
-      const C<T> alpha = mk<T>(qr_re * iq, qr_im * iq);
+    for (int c = 0; c < 6; ++c) o[c] = mk<T>(rfma(T(-0.5), h[c].x, o[c].x), rfma(T(-0.5), h[c].y, o[c].y));
+  };
+
+  C<T> rho[6], x[6], q[6];
 #pragma unroll
-      for (int c = 0; c < 12; ++c) {
-        cfma(x[c], alpha, rho[c]);
-        cfma(rho[c], mk<T>(-alpha.x, -alpha.y), q[c]);
-      }
-      __syncthreads();
+  for (int c = 0; c < 6; ++c) {
+    rho[c] = decode(zkeep[c], zsk);
+    own[c * 16] = rho[c];
+    x[c] = czero<T>();
+  }
+  __syncthreads();
+  pair_outer<T, S, V, 0>(op, z, zs, blk, loc, p, nb4.x, nb4.y, acc);
+  pair_outer<T, S, V, 1>(op, z, zs, blk, loc, p, nb4.z, nb4.w, acc);
+  inblock(std::false_type{});
+  diag(rho, q);
+#pragma unroll
+  for (int c = 0; c < 6; ++c) {
+    const C<T> bb = decode(braw[c], bsk);
+    rho[c] = mk<T>(bb.x - q[c].x, bb.y - q[c].y);
+  }
+
+  for (int it = 0; it < mr_iters; ++it) {
+    __syncthreads();
+#pragma unroll
+    for (int c = 0; c < 6; ++c) own[c * 16] = rho[c];
+    __syncthreads();
+    inblock(std::true_type{});
+    diag(rho, q);
+    T qr_re = 0, qr_im = 0, qq = 0;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      qr_re = rfma(q[c].x, rho[c].x, qr_re);
+      qr_re = rfma(q[c].y, rho[c].y, qr_re);
+      qr_im = rfma(q[c].x, rho[c].y, qr_im);
+      qr_im = rfma(-q[c].y, rho[c].x, qr_im);
+      qq = rfma(q[c].x, q[c].x, qq);
+      qq = rfma(q[c].y, q[c].y, qq);
     }
-    if (valid) {
-      // z + x (for FP16 spinors re-encoded with the site's new scale)
-      C<T> zz[12];
-      if constexpr (KZ) decode_kept<T, V>(zkeep, zsk, zz);
-      else load_site<T, V>(z, zs, blk, loc, zz);
+    qr_re = block_sum<T>(qr_re);
+    qr_im = block_sum<T>(qr_im);
+    qq = block_sum<T>(qq);
+    const T iq = qq > T(0) ? T(1) / qq : T(0);
+    const C<T> alpha = mk<T>(qr_re * iq, qr_im * iq);
 #pragma unroll
-      for (int c = 0; c < 12; ++c) zz[c] = cadd(zz[c], x[c]);
-      store_site<T, V, NT>(z, zs, blk, loc, zz);
+    for (int c = 0; c < 6; ++c) {
+      cfma(x[c], alpha, rho[c]);
+      cfma(rho[c], mk<T>(-alpha.x, -alpha.y), q[c]);
+    }
+  }
+  // z + x (for FP16 spinors re-encoded with the site's new scale)
+#pragma unroll
+  for (int c = 0; c < 6; ++c) x[c] = cadd(decode(zkeep[c], zsk), x[c]);
+  if constexpr (HS) {
+    float m = 0.f;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) m = fmaxf(m, fmaxf(fabsf(x[c].x), fabsf(x[c].y)));
+    float m2 = m;
+    row_swap(m, m2);
+    m = fmaxf(m, m2);
+    const float inv = m > 0.f ? 1.f / m : 0.f;
+    if (p == 0) zs[sc] = m;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      const __half2 h = __floats2half2_rn(x[c].x * inv, x[c].y * inv);
+      if constexpr (NT) store_nt(z + so + c * 16, h);
+      else z[so + c * 16] = h;
+    }
+  } else {
+#pragma unroll
+    for (int c = 0; c < 6; ++c) {
+      if constexpr (NT) store_nt(z + so + c * 16, x[c]);
+      else z[so + c * 16] = x[c];
     }
   }
 }
@@ -1033,9 +1063,9 @@ void sap_colour(const FineOpView<T, S>& op, const int* colour_blocks, int colour
                 const C<T>* b, C<T>* z, hipStream_t s, int nb) {
   const int ncb = op.nblk / 2;
   const long long fs = (long long)op.nblk * 192;
-  const unsigned gx = nblocks(ncb, SAP_WG / 16);
+  const unsigned gx = ncb / 2;   // (extents are multiples of 4: a colour has 8k blocks)
   const auto k = op_streams<S>(op.nblk, nb) ? k_sap_colour<T, S, C<T>, true> : k_sap_colour<T, S, C<T>, false>;
-  k<<<gx * nb, SAP_WG, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, nullptr, z, nullptr, nb, fs, (int)gx);
+  k<<<gx * nb, SAP_WG, 0, s>>>(op, colour_blocks + colour * ncb, mr_iters, b, nullptr, z, nullptr, nb, fs, (int)gx);
   DD_LAUNCH_CHECK();
 }
 
@@ -1043,10 +1073,10 @@ void sap_colour_hs(const FineOpView<float, __half2>& op, const int* colour_block
                    const __half2* b, const float* bs, __half2* z, float* zs, hipStream_t s, int nb) {
   const int ncb = op.nblk / 2;
   const long long fs = (long long)op.nblk * 192;
-  const unsigned gx = nblocks(ncb, SAP_WG / 16);
+  const unsigned gx = ncb / 2;   // (extents are multiples of 4: a colour has 8k blocks)
   const auto k = op_streams<__half2>(op.nblk, nb) ? k_sap_colour<float, __half2, __half2, true>
                                                   : k_sap_colour<float, __half2, __half2, false>;
-  k<<<gx * nb, SAP_WG, 0, s>>>(op, colour_blocks + colour * ncb, ncb, mr_iters, b, bs, z, zs, nb, fs, (int)gx);
+  k<<<gx * nb, SAP_WG, 0, s>>>(op, colour_blocks + colour * ncb, mr_iters, b, bs, z, zs, nb, fs, (int)gx);
   DD_LAUNCH_CHECK();
 }
 

@@ -77,7 +77,9 @@ __device__ inline int xcd_slab_index(int bid, int nwg) {
 // it between one chunk and its neighbours for the chunks' faces to be still
 // there.  12 fields on 16^3x32, FP32, stencil in us for groups of 1, 2, 3, 4, 6,
 // 12: 258, 183, 174, 168, 166, 166 (inputs in the last-level cache; else 3: 209,
-// 4: 208, 6: 209, 12: 216); five FP32 SAP sweeps 2157, 1652, 1586, 1554, 1464, 1564.  Sets the workgroup's block-chunk index x and field r.
+// 4: 208, 6: 209, 12: 216); five FP32 SAP sweeps (one lane a
+// site): 2157, 1652, 1586, 1554, 1464, 1564.  Sets the workgroup's block-chunk
+// index x and field r.
 constexpr int XCD_FIELDS = 6;
 __device__ inline void xcd_slab_rhs(int bid, int gx, int nb, int& x, int& r) {
   if (gx % 8 != 0) {
@@ -209,10 +211,10 @@ __device__ inline void load_link(const S* __restrict__ U, int blk, int loc, C<T>
   for (int k = 0; k < 9; ++k) u[k] = ldc<T, S>(e[k]);
 }
 
-// out = A(x) v for the packed clover of one site (both chiralities); get(e)
-// returns entry e = 0..35 as C<T>: per chirality 3 packed real diagonal
-// pairs, then the 15 upper off-diagonal entries row by row
-// one chirality block h of the clover: o = A_h w (6 components each)
+// The packed clover of one site; get(e) returns entry e = 0..35 as C<T>: per
+// chirality 3 packed real diagonal pairs, then the 15 upper off-diagonal
+// entries row by row.
+// One chirality block h of the clover: o = A_h w (6 components each)
 template <typename T, typename G>
 __device__ inline void clover_block(int h, G&& get, const C<T>* w, C<T>* o) {
 #pragma unroll
@@ -231,12 +233,6 @@ __device__ inline void clover_block(int h, G&& get, const C<T>* w, C<T>* o) {
       cfma(o[a], m, w[b]);
       cjfma(o[b], m, w[a]);
     }
-}
-
-template <typename T, typename G>
-__device__ inline void clover_mul(G&& get, const C<T> v[12], C<T> out[12]) {
-#pragma unroll
-  for (int h = 0; h < 2; ++h) clover_block<T>(h, get, v + 6 * h, out + 6 * h);
 }
 
 template <typename T, typename S = C<T>, bool NT = false>
