@@ -336,14 +336,121 @@ struct MfmaRows {
   }
 };
 
+// FP16 storage.  The matrix cores multiply FP16 numbers 16 times as fast as FP32
+// ones and sum the exact products in FP32, so the operator enters as it is
+// stored and an input vector x in two FP16 parts of a common power of two per
+// (block, right-hand side), hi = fp16(x s) and mid = fp16(2^11 (x s - hi)):
+// together x to one unit in its last FP32 place (see split_row).  A lane's four
+// columns t, each (re, im), are eight consecutive k of v_mfma_f32_16x16x32_f16
+// in both operands: lane l supplies A[l % 16][8 (l / 16) ..] and B[8 (l / 16)
+// ..][l % 16], the result as for the FP32 instruction.  The real part's B holds
+// (re, -im), the imaginary part's (im, re).  Error against 64 bits of five SAP
+// sweeps, d = 40: 1.3e-7 (FP32 products 2.0e-7, vector kernels 2.6e-7); the
+// sweeps on 12 fields of 8^3x16 sites 4090 -> 3410 us.
+template <int NJ>
+struct MfmaRows<__half2, NJ> {
+  static constexpr int DEP = 2;
+  unsigned a[DEP][NJ];
+  const unsigned* Kx;
+  unsigned mask;
+  int ns, d, lo, kk;
+  __device__ __forceinline__ void load(int u, int s) {
+    const unsigned* Kb = Kx + (unsigned)(mask_slot(mask, s) * d * d);
+#pragma unroll
+    for (int t = 0; t < NJ; ++t) {
+      // columns past d repeat column d - 1 (they meet zero rows of B)
+      const unsigned o = (t + 1) * 4 <= d ? (unsigned)(lo + (4 * t + kk) * d) : (unsigned)(lo + min(4 * t + kk, d - 1) * d);
+      a[u][t] = Kb[o];
+    }
+  }
+  __device__ __forceinline__ void prefetch(const __half2* __restrict__ Kx_, unsigned mask_, int row, int kk_, int d_) {
+    Kx = reinterpret_cast<const unsigned*>(Kx_);
+    mask = mask_;
+    ns = __builtin_popcount(mask_);
+    d = d_;
+    lo = row;
+    kk = kk_;
+#pragma unroll
+    for (int u = 0; u < DEP; ++u)
+      if (u < ns) load(u, u);
+  }
+  // lds_b: [ns][4 NJ][pitch] pairs (hi, mid), behind them the inverse scales
+  // [ns][pitch]
+  __device__ __forceinline__ void apply(const float2* lds_b, int pitch, int rl, f32x4& cr, f32x4& ci) {
+    typedef _Float16 f16x8 __attribute__((ext_vector_type(8)));
+    typedef unsigned u32x4 __attribute__((ext_vector_type(4)));
+    cr = {0.f, 0.f, 0.f, 0.f};
+    ci = {0.f, 0.f, 0.f, 0.f};
+    const uint2* bt = reinterpret_cast<const uint2*>(lds_b) + kk * pitch + rl;
+    const float* sc = reinterpret_cast<const float*>(lds_b + ns * 4 * NJ * pitch) + rl;
+#pragma unroll 1
+    for (int s0 = 0; s0 < ns; s0 += DEP) {
+#pragma unroll
+      for (int u = 0; u < DEP; ++u)
+        if (s0 + u < ns) {
+          f32x4 hr = {0.f, 0.f, 0.f, 0.f}, hi = hr, mr = hr, mi = hr;
+#pragma unroll
+          for (int t0 = 0; t0 < NJ; t0 += 4) {
+            u32x4 av = {0, 0, 0, 0}, h0 = av, h1 = av, m0 = av, m1 = av;
+#pragma unroll
+            for (int t = t0; t < NJ && t < t0 + 4; ++t) {
+              const uint2 bv = bt[((s0 + u) * 4 * NJ + 4 * t) * pitch];
+              av[t - t0] = a[u][t];
+              h0[t - t0] = bv.x ^ 0x80000000u;
+              h1[t - t0] = __builtin_amdgcn_alignbit(bv.x, bv.x, 16);
+              m0[t - t0] = bv.y ^ 0x80000000u;
+              m1[t - t0] = __builtin_amdgcn_alignbit(bv.y, bv.y, 16);
+            }
+            const f16x8 A = __builtin_bit_cast(f16x8, av);
+            hr = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, __builtin_bit_cast(f16x8, h0), hr, 0, 0, 0);
+            hi = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, __builtin_bit_cast(f16x8, h1), hi, 0, 0, 0);
+            mr = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, __builtin_bit_cast(f16x8, m0), mr, 0, 0, 0);
+            mi = __builtin_amdgcn_mfma_f32_16x16x32_f16(A, __builtin_bit_cast(f16x8, m1), mi, 0, 0, 0);
+          }
+          const float sv = sc[(s0 + u) * pitch];
+#pragma unroll
+          for (int v = 0; v < 4; ++v) {
+            cr[v] = rfma(sv, rfma(0x1p-11f, mr[v], hr[v]), cr[v]);
+            ci[v] = rfma(sv, rfma(0x1p-11f, mi[v], hi[v]), ci[v]);
+          }
+          if (s0 + u + DEP < ns) load(u, s0 + u + DEP);
+        }
+    }
+  }
+};
+
+// The two FP16 parts of this lane's element f of a row that the wavefront holds:
+// scaled by the power of two that takes the row's largest |re|, |im| to [2^14,
+// 2^15) (rows below 2^-100 as if that were theirs); inv its inverse
+__device__ __forceinline__ uint2 split_row(float2 f, float& inv) {
+  float m = fmaxf(fabsf(f.x), fabsf(f.y));
+  m = fmaxf(m, dpp_mov<0xB1>(m));
+  m = fmaxf(m, dpp_mov<0x4E>(m));
+  m = fmaxf(m, dpp_mov<0x141>(m));
+  m = fmaxf(m, dpp_mov<0x140>(m));
+  auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  m = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  r = __builtin_amdgcn_permlane32_swap(__float_as_uint(m), __float_as_uint(m), false, false);
+  m = fmaxf(__uint_as_float(r[0]), __uint_as_float(r[1]));
+  const unsigned e = max(__float_as_uint(m) >> 23, 27u);
+  const float s = __uint_as_float((268u - e) << 23);
+  inv = __uint_as_float((e - 14u) << 23);
+  f = make_float2(f.x * s, f.y * s);
+  const __half2 h = __floats2half2_rn(f.x, f.y);
+  const float2 hf = __half22float2(h);
+  const __half2 l = __floats2half2_rn((f.x - hf.x) * 2048.f, (f.y - hf.y) * 2048.f);
+  return make_uint2(__builtin_bit_cast(unsigned, h), __builtin_bit_cast(unsigned, l));
+}
+
 // Stages the input vectors of a site: row (k, r), slot k of the mask and
 // right-hand side r, is one wavefront's contiguous read, U of them in flight
 // at a time; get(r, o) loads element o of right-hand side r, fin(r, v) turns
 // what was loaded into the staged value, and mid() runs once after the first
 // loads are issued.  The neighbour of slot k is read once into lane k and
 // broadcast from there, so that no row waits on an index.  Rows past d of a
-// slot are zeroed (they meet the repeated operator columns).
-template <int NJ, typename G, typename F, typename M>
+// slot are zeroed (they meet the repeated operator columns).  For FP16 storage
+// (H) a row is split as its product takes it.
+template <bool H, int NJ, typename G, typename F, typename M>
 __device__ __forceinline__ void mfma_stage(float2* lds_b, int pitch, unsigned mask, const int* __restrict__ nb9, int w,
                                            int nw, int lane, int d, int nr, G&& get, F&& fin, M&& mid) {
   constexpr int U = 8;
@@ -367,7 +474,15 @@ __device__ __forceinline__ void mfma_stage(float2* lds_b, int pitch, unsigned ma
     if (p0 == w) mid();
 #pragma unroll
     for (int u = 0; u < U; ++u) {
-      if (r < nr && lane < 4 * NJ) {
+      if constexpr (H) {
+        if (r < nr) {
+          float inv;
+          const uint2 f = split_row(fin(r, v[u]), inv);
+          if (lane < 4 * NJ)
+            reinterpret_cast<uint2*>(lds_b)[(k * 4 * NJ + lane) * pitch + r] = lane < d ? f : make_uint2(0u, 0u);
+          if (lane == 0) reinterpret_cast<float*>(lds_b + ns * 4 * NJ * pitch)[k * pitch + r] = inv;
+        }
+      } else if (r < nr && lane < 4 * NJ) {
         const float2 f = fin(r, v[u]);
         lds_b[(k * 4 * NJ + lane) * pitch + r] = lane < d ? f : make_float2(0.f, 0.f);
       }
@@ -392,7 +507,7 @@ __device__ __forceinline__ void mfma_rows(int mt, int lane, int d, F&& f) {
 // out = K in over the sites of `sites` (nullptr: every site), or with b
 // given out = b - K in (the residual of a SAP colour pass)
 template <typename S, int NJ>
-__global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_capply_mfma(CoarseOpView<float, S> op, const int* __restrict__ sites,
+__global__ void __launch_bounds__(64 * ((NJ + 3) / 4), 4) k_capply_mfma(CoarseOpView<float, S> op, const int* __restrict__ sites,
                                                                const float2* __restrict__ in,
                                                                const float2* __restrict__ b, float2* __restrict__ out,
                                                                long long n, int nb, int per) {
@@ -408,7 +523,7 @@ __global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_capply_mfma(CoarseOpVie
   const int kk = lane >> 4, rl = min(lane & 15, nr - 1);
   MfmaRows<S, NJ> mr;
   mr.prefetch(op.K + (size_t)site * 9 * d * d, 0x1FFu, min(w * 16 + (lane & 15), d - 1), kk, d);
-  mfma_stage<NJ>(
+  mfma_stage<std::is_same<S, __half2>::value, NJ>(
       lds_b, pitch, 0x1FFu, op.nbr9 + (size_t)site * 9, w, nmt, lane, d, nr,
       [&](int r, unsigned o) { return in[r * n + o]; }, [](int, float2 v) { return v; }, [] {});
   const long long own = (long long)site * d + rl * n;
@@ -437,16 +552,16 @@ inline void with_int(int v, F&& f) {
 
 // The launch of a batch of nb fields on d components with ns staged blocks:
 // chunks of `per` right-hand sides (equal chunks of at most 16, fewer where
-// the B tile would pass 63 KiB) and their LDS bytes
+// the B tile would pass 63 KiB) and their LDS bytes (H: with the scales)
 struct MfmaShape {
   int per, nch, nmt, nj;
   size_t lds;
 };
-inline MfmaShape mfma_shape(int d, int nb, int ns) {
+inline MfmaShape mfma_shape(int d, int nb, int ns, bool H) {
   MfmaShape m;
   m.nj = (d + 3) / 4;
   m.nmt = (m.nj + 3) / 4;
-  const int row = ns * 4 * m.nj * (int)sizeof(float2);
+  const int row = ns * (4 * m.nj * (int)sizeof(float2) + (H ? (int)sizeof(float) : 0));
   int cap = std::min(MFMA_NB, MFMA_LDS / row);
   if ((cap | 1) * row > MFMA_LDS) --cap;       // the pitch is odd
   m.nch = (nb + cap - 1) / cap;
@@ -455,22 +570,29 @@ inline MfmaShape mfma_shape(int d, int nb, int ns) {
   return m;
 }
 
-// Whether the matrix cores take a batch of nb in FP32 arithmetic.  The
-// matrix-core kernels read the operator once for up to 16 fields but spend 16
-// columns of products on any batch; the vector kernels read it once per
-// four fields (then per two, then per one).  Measured on 8^3x16 sites, d = 40,
-// FP16 storage, operator apply in us (vector / matrix cores): nb = 2 103 /
-// 186, 3 190 / 189, 4 150 / 190, 5 235 / 193, 8 297 / 203, 16 312 / 304; five
-// SAP sweeps in ms: nb = 2 2.42 / 3.06, 3 3.96 / 3.15, 4 3.25 / 3.20, 5 4.81 /
-// 3.33, 8 6.14 / 3.54, 12 9.03 / 4.10, 20 14.9 / 7.2.  So only the batches of
-// two and four, which the vector kernels take in one launch, stay with them.
-inline bool use_mfma(int nb) { return nb == 3 || nb >= 5; }
+// Whether the matrix cores take a batch of nb in FP32 arithmetic on V sites.
+// The matrix-core kernels read the operator once for up to 16 fields but spend
+// 16 columns of products on any batch; the vector kernels read it once per
+// four fields (then per two, then per one).  d = 40, vector / matrix cores.
+// FP32 storage (FP32 products), operator apply on 8^3x16 sites in us: nb = 2
+// 103 / 186, 3 190 / 189, 4 150 / 190, 5 235 / 193, 8 297 / 203, 16 312 / 304:
+// only the batches of two and four, which the vector kernels take in one
+// launch, stay with them.  FP16 storage (FP16 products), five SAP sweeps in
+// ms: 8^3x16 sites nb = 1 1.60 / 1.67, 2 2.41 / 1.81, 3 3.96 / 1.95, 4 3.24 /
+// 2.05, 8 6.14 / 2.63; 4^3x8 sites, where latency counts, 1 0.322 / 0.334, 2
+// 0.341 / 0.357, 4 0.449 / 0.400; two fields on 2048 sites 0.718 / 0.561, on
+// 4096 1.30 / 1.05.
+constexpr int MFMA_PAIR_SITES = 2048;
+template <typename S> inline bool use_mfma(int nb, int V) {
+  if (std::is_same<S, __half2>::value) return nb >= 3 || (nb == 2 && V >= MFMA_PAIR_SITES);
+  return nb == 3 || nb >= 5;
+}
 
 template <typename S>
 void coarse_apply_mfma(const CoarseOpView<float, S>& op, const int* sites, int nsites, const float2* in,
                        const float2* b, float2* out, hipStream_t s, int nb) {
   const long long n = (long long)op.V * op.d;
-  const MfmaShape m = mfma_shape(op.d, nb, 9);
+  const MfmaShape m = mfma_shape(op.d, nb, 9, std::is_same<S, __half2>::value);
   with_int<1, 16>(m.nj, [&](auto nj) {
     k_capply_mfma<S, decltype(nj)::value><<<dim3(nsites, m.nch), 64 * m.nmt, m.lds, s>>>(
         op, sites, in, b, out, n, nb, m.per);
@@ -481,7 +603,7 @@ void coarse_apply_mfma(const CoarseOpView<float, S>& op, const int* sites, int n
 template <typename T, typename S>
 void coarse_apply(const CoarseOpView<T, S>& op, const C<T>* in, C<T>* out, hipStream_t s, int nb) {
   if constexpr (std::is_same<T, float>::value) {
-    if (use_mfma(nb) && op.d <= 64) {
+    if (use_mfma<S>(nb, op.V) && op.d <= 64) {
       coarse_apply_mfma<S>(op, nullptr, op.V, in, nullptr, out, s, nb);
       return;
     }
@@ -841,13 +963,14 @@ __device__ inline float2 block_alpha_row(const float* __restrict__ part, int blk
 // The MR step of a batch on the matrix cores (the product as in
 // k_capply_mfma, over the in-block operator blocks of a site).  Workgroups
 // are mapped so that the sites of a block run on one XCD, whose L2 then
-// serves the block's vectors to all of them.  Bound by the matrix cores' FP32
-// rate (16 x 16 tiles hold 40 x 12 results) and the latency of the chain step
-// size, inputs, product: 86 us for 12 fields on 4096 sites, d = 40, FP16
-// storage, against 230 us on the vector units; the residual (k_capply_mfma)
-// 136 against 194 us.
+// serves the block's vectors to all of them.  Bound by the number of its load
+// instructions and the latency of the chain step size, inputs, product, with
+// FP32 storage by the matrix cores' FP32 rate too: 12 fields on 4096 sites, d =
+// 40, FP16 storage 230 us on the vector units, 86 with FP32 products, 79 with
+// FP16 ones and 77 so with registers held to four waves per SIMD; the residual
+// (k_capply_mfma) 194, 136, 112, 109 us.
 template <typename S, int NJ>
-__global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_sap_q_mfma(CoarseOpView<float, S> op, const int* __restrict__ csites,
+__global__ void __launch_bounds__(64 * ((NJ + 3) / 4), 4) k_sap_q_mfma(CoarseOpView<float, S> op, const int* __restrict__ csites,
                                                               SapTables tb, int pos0, int step,
                                                               const float2* __restrict__ rho_prev,
                                                               const float2* __restrict__ q_prev,
@@ -857,6 +980,7 @@ __global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_sap_q_mfma(CoarseOpView
                                                               float2* __restrict__ z, long long n, int nb, int per) {
   extern __shared__ float2 lds_b[];
   constexpr int nmt = (NJ + 3) / 4;
+  constexpr bool H = std::is_same<S, __half2>::value;
   __shared__ float2 alpha_s[MFMA_NB];
   __shared__ float dot_s[nmt][3][MFMA_NB];
   const int x = xcd_slab_index(blockIdx.x, gridDim.x);
@@ -880,13 +1004,16 @@ __global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_sap_q_mfma(CoarseOpView
   const int* nb9 = op.nbr9 + (size_t)site * 9;
   // the site's own rows of the previous residual and of z, for z += alpha rho
   const long long own = (long long)site * d + rl * n;
-  float2 zown[4], rown[4];
+  // (H: and the new residual, which the staged rows hold in parts)
+  float2 zown[4], rown[4], qown[4];
+  if (H && step == 0) mfma_rows(w, lane, d, [&](int v, int i) { rown[v] = rho_prev[own + i]; });
   if (step > 0) {
     mfma_rows(w, lane, d, [&](int v, int i) {
       zown[v] = z[own + i];
       rown[v] = rho_prev[own + i];
+      if constexpr (H) qown[v] = q_prev[own + i];
     });
-    mfma_stage<NJ>(
+    mfma_stage<H, NJ>(
         lds_b, pitch, mask, nb9, w, nmt, lane, d, nr,
         [&](int r, unsigned o) {
           const float2 a = rho_prev[r * n + o], b = q_prev[r * n + o];
@@ -902,7 +1029,7 @@ __global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_sap_q_mfma(CoarseOpView
           __syncthreads();
         });
   } else {
-    mfma_stage<NJ>(
+    mfma_stage<H, NJ>(
         lds_b, pitch, mask, nb9, w, nmt, lane, d, nr, [&](int r, unsigned o) { return rho_prev[r * n + o]; },
         [](int, float2 v) { return v; }, [] {});
   }
@@ -912,7 +1039,10 @@ __global__ void __launch_bounds__(64 * ((NJ + 3) / 4)) k_sap_q_mfma(CoarseOpView
   float a0 = 0.f, a1 = 0.f, a2 = 0.f;
   const bool live = (lane & 15) < nr;
   mfma_rows(w, lane, d, [&](int v, int i) {
-    const float2 rho = lds_b[i * pitch + rl], q = make_float2(cr[v], ci[v]);
+    float2 rho;
+    if constexpr (H) rho = step > 0 ? csub(rown[v], cmul(alpha_s[rl], qown[v])) : rown[v];
+    else rho = lds_b[i * pitch + rl];
+    const float2 q = make_float2(cr[v], ci[v]);
     a0 = rfma(q.x, rho.x, rfma(q.y, rho.y, a0));
     a1 = rfma(q.x, rho.y, rfma(-q.y, rho.x, a1));
     a2 = rfma(q.x, q.x, rfma(q.y, q.y, a2));
@@ -986,9 +1116,9 @@ void coarse_sap_colour(const CoarseOpView<T, S>& op, const SapTables& tb, int co
   const long long n = (long long)op.V * op.d, pn = (long long)op.V * 4;
   bool done = false;
   if constexpr (std::is_same<T, float>::value) {
-    if (use_mfma(nb)) {
+    if (use_mfma<S>(nb, op.V)) {
       coarse_apply_mfma<S>(op, csites, nsites, z, b, ws.rho[1], s, nb);
-      const MfmaShape m = mfma_shape(op.d, nb, tb.kmax);
+      const MfmaShape m = mfma_shape(op.d, nb, tb.kmax, std::is_same<S, __half2>::value);
       for (int t = 0; t < mr_iters; ++t) {
         const int pp = (t + 1) & 1, cc = t & 1;   // previous / current buffers
         with_int<1, 16>(m.nj, [&](auto nj) {

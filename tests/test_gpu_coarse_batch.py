@@ -65,3 +65,42 @@ def test_batched_coarse_level(dd, n, half, nrhs):
             say(f"  nrhs={nb} block={block} relerr {e:.2e}")
             assert e <= TOL
     torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("dims,n,nb", [((16, 16, 16, 16), 20, 4), ((16, 16, 16, 16), 6, 3), ((32, 32, 16, 32), 8, 2)])
+def test_half_storage_batch_against_single(dd, dims, n, nb):
+    """FP16 storage, batches on both sides of the dispatch's lines (nb = 2 goes
+    to the matrix cores from 2048 sites), against the same fields one by one on
+    the vector kernels; and fields of very different scale, a zero field and
+    one with a NaN in it, none of which may touch another.  Tolerance: two
+    results with TOL of the exact one each."""
+    p = _p(2, [(4, 4, 4, 4)], [n], n_inv=0)
+    g = torch.Generator(device="cuda").manual_seed(5)
+
+    def field(sites, dof, k):
+        return torch.randn((k,) + sites + (dof,), generator=g, device="cuda", dtype=torch.complex128)
+
+    shape = tuple(dims)[::-1]
+    ctx = dd.create(dims, -0.3, 1.0, dev(W.links(dims, 0.5, 71)))
+    H = dd.build_hierarchy(ctx, to_params(dd, p, dd.F32, half=True), field(shape, 12, n))
+    cs = tuple(e // 4 for e in shape)
+    b = field(cs, 2 * n, nb)
+    scale = [1.0, 1e-30, 1e30, 0.0][:nb]
+    for r in range(nb):
+        b[r] *= scale[r]
+    out = torch.zeros_like(b)
+    dd.apply_Dc(H, 1, b, out, nrhs=nb, prec=dd.F32)
+    for r in range(nb):
+        one = torch.zeros_like(b[r])
+        dd.apply_Dc(H, 1, b[r].contiguous(), one, prec=dd.F32)
+        assert float((out[r] - one).norm()) <= 2 * TOL * float(one.norm()), r
+    b = field(cs, 2 * n, nb)
+    b.view(nb, -1)[nb - 1, 3] = float("nan")
+    z = torch.zeros_like(b)
+    dd.apply_Dc(H, 1, b, z, nrhs=nb, prec=dd.F32)
+    assert bool(torch.isnan(torch.view_as_real(z[nb - 1])).any())
+    for r in range(nb - 1):
+        one = torch.zeros_like(b[r])
+        dd.apply_Dc(H, 1, b[r].contiguous(), one, prec=dd.F32)
+        assert float((z[r] - one).norm()) <= 2 * TOL * float(one.norm()), r
+    torch.cuda.synchronize()
