@@ -246,28 +246,37 @@ __global__ void __launch_bounds__(64 * SW) k_capply(CoarseOpView<T, S> op, const
     for (int r = 0; r < RB; ++r) out[r * n + (size_t)site * d + lane] = acc[r];
 }
 
-// Whether the matrix cores take a batch of nb in FP32 arithmetic on V sites.
-// The matrix-core kernels read the operator once for up to 16 fields but spend
-// 16 columns of products on any batch; the vector kernels read it once per
-// four fields (then per two, then per one).  d = 40, vector / matrix cores.
-// FP32 storage (FP32 products), operator apply on 8^3x16 sites in us: nb = 2
-// 103 / 186, 3 190 / 189, 4 150 / 190, 5 235 / 193, 8 297 / 203, 16 312 / 304:
-// only the batches of two and four, which the vector kernels take in one
-// launch, stay with them.  FP16 storage (FP16 products), five SAP sweeps in
-// ms: 8^3x16 sites nb = 1 1.60 / 1.67, 2 2.41 / 1.81, 3 3.96 / 1.95, 4 3.24 /
-// 2.05, 8 6.14 / 2.63; 4^3x8 sites, where latency counts, 1 0.322 / 0.334, 2
-// 0.341 / 0.357, 4 0.449 / 0.400; two fields on 2048 sites 0.718 / 0.561, on
-// 4096 1.30 / 1.05.
+// Whether the matrix cores take a batch of nb fields of d components in FP32
+// arithmetic on V sites.  The matrix-core kernels read the operator once for up
+// to 16 fields but spend 16 columns of products on any batch; the vector kernels
+// read it once per four fields (then per two, then per one) and take multiples
+// of four in one launch.  One SAP sweep / operator apply in us, vector / matrix
+// cores, on 256, 2048 and 4096 sites:
+//   FP16 storage, d = 16, nb = 2: 48/49 7.5/7.6, 65/63 9.0/7.7, 109/76 16/13
+//                         nb = 4: 60/50 7.5/7.7, 110/65 13/7.7, 198/82 24/13
+//                         nb = 12: 70/53 7.5/7.7, 277/81 34/11, 521/120 65/19
+//   FP16 storage, d = 40, nb = 2: 66/67 7.3/7.7, 141/119 27/26, 257/217 46/46
+//                         nb = 4: 86/71 7.9/7.7, 196/135 37/32, 348/248 65/53
+//                         nb = 12: 111/97 15/12, 484/213 91/54, 915/392 175/100
+//   FP32 storage, d = 40, nb = 2: 73/84 7.8/11, 248/189 61/54, 493/369 144/112
+//                         nb = 3: 128/85 15/12, 410/194 114/57, 798/384 275/112
+//                         nb = 4: 92/86 9.8/12, 308/197 76/57, 612/389 174/114
+//                         nb = 8: 94/90 18/13, 575/225 147/58, 1162/427 349/122
+// So FP16 storage goes to them from three fields and from two where the sites
+// fill the device (not with d = 8, apply 9.1/10.5 us on 4096 sites, nor d = 56,
+// sweep 378/394: there only three).  With FP32 storage two and four fields stay
+// with the vector kernels, which need one launch for them on small lattices.
 constexpr int MFMA_PAIR_SITES = 2048;
-template <typename S> inline bool use_mfma(int nb, int V) {
-  if (std::is_same<S, __half2>::value) return nb >= 3 || (nb == 2 && V >= MFMA_PAIR_SITES);
+template <typename S> inline bool use_mfma(int nb, int V, int d) {
+  if (std::is_same<S, __half2>::value)
+    return nb >= 3 || (nb == 2 && V >= MFMA_PAIR_SITES && d >= 12 && (d <= 48 || d > 60));
   return nb == 3 || nb >= 5;
 }
 
 template <typename T, typename S>
 void coarse_apply(const CoarseOpView<T, S>& op, const C<T>* in, C<T>* out, hipStream_t s, int nb) {
   if constexpr (std::is_same<T, float>::value) {
-    if (use_mfma<S>(nb, op.V) && op.d <= 64) {
+    if (use_mfma<S>(nb, op.V, op.d) && op.d <= 64) {
       coarse_apply_mfma<S>(op, nullptr, op.V, in, nullptr, out, s, nb);
       return;
     }
@@ -646,14 +655,13 @@ void coarse_sap_colour(const CoarseOpView<T, S>& op, const SapTables& tb, int co
   const long long n = (long long)op.V * op.d, pn = (long long)op.V * 4;
   bool done = false;
   if constexpr (std::is_same<T, float>::value) {
-    if (use_mfma<S>(nb, op.V)) {
+    if (use_mfma<S>(nb, op.V, op.d)) {
       coarse_apply_mfma<S>(op, csites, nsites, z, b, ws.rho[1], s, nb);
       for (int t = 0; t < mr_iters; ++t) coarse_sap_q_mfma<S>(op, tb, csites, nsites, pos0, t, z, ws, s, nb);
       done = true;
     }
   }
-  if (!done)
-  with_nch(op.d, [&](auto nch) {
+  if (!done) with_nch(op.d, [&](auto nch) {
     constexpr int NCH = decltype(nch)::value;
     rhs_chunks<T>(nb, [&](auto rb, int first, int nc) {
       constexpr int RB = decltype(rb)::value;

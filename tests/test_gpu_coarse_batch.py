@@ -104,3 +104,71 @@ def test_half_storage_batch_against_single(dd, dims, n, nb):
         dd.apply_Dc(H, 1, b[r].contiguous(), one, prec=dd.F32)
         assert float((z[r] - one).norm()) <= 2 * TOL * float(one.norm()), r
     torch.cuda.synchronize()
+
+
+# groups of wavefronts per row tile (1, 2, 4) and lanes per staged row (8, 16, 32,
+# 64) of the matrix-core kernels over d and the number of sites: 4^4 sites take
+# the most groups, 8^4 the fewest; 16 FP32 fields of d = 56 the even pitch
+@pytest.mark.parametrize("e,n,half,nb", [(16, 4, True, 5), (16, 4, False, 16), (16, 7, True, 9), (16, 10, False, 3),
+                                         (16, 28, False, 16), (32, 4, True, 3), (32, 4, False, 17), (32, 8, True, 9),
+                                         (32, 13, False, 3), (32, 13, True, 9), (32, 20, False, 5), (32, 22, True, 11),
+                                         (32, 28, False, 16), (32, 32, True, 3)])
+def test_batch_shapes_against_single(dd, e, n, half, nb):
+    """Operator and two SAP sweeps of a batch against its fields one by one (the
+    vector kernels).  Tolerance: two results with TOL of the exact one each."""
+    say(f"coarse shapes e={e} d={2 * n} half={half} nb={nb}")
+    g = torch.Generator(device="cuda").manual_seed(11)
+
+    def field(*shape):
+        return torch.randn(shape, generator=g, device="cuda", dtype=torch.complex128)
+
+    dims = (e,) * 4
+    p = _p(3, [(4, 4, 4, 4), (2, 2, 2, 2)], [n, 4], n_inv=0)
+    ctx = dd.create(dims, 1.0, 1.0, 0.3 * field(e, e, e, e, 4, 3, 3))
+    H = dd.build_hierarchy(ctx, to_params(dd, p, dd.F32, half=half), field(n, e, e, e, e, 12))
+    b, z0 = (field(nb, *((e // 4,) * 4), 2 * n) for _ in range(2))
+    out, z = torch.zeros_like(b), z0.clone()
+    dd.apply_Dc(H, 1, b, out, nrhs=nb, prec=dd.F32)
+    dd.sap_smooth(H, 1, b, z, 2, nrhs=nb, prec=dd.F32)
+    for r in range(nb):
+        one, zr = torch.zeros_like(b[r]), z0[r].clone()
+        dd.apply_Dc(H, 1, b[r].contiguous(), one, prec=dd.F32)
+        dd.sap_smooth(H, 1, b[r].contiguous(), zr, 2, prec=dd.F32)
+        assert float((out[r] - one).norm()) <= 2 * TOL * float(one.norm()), r
+        assert float((z[r] - zr).norm()) <= 2 * TOL * float(zr.norm()), r
+
+
+@pytest.mark.parametrize("e,n,nb,bound", [(16, 4, 16, 2.5), (16, 8, 12, 2.5), (32, 8, 16, 4.0)])
+def test_batch_time(dd, e, n, nb, bound):
+    """A batch of small blocks costs little more than one field: on 4^4 sites, where
+    latency counts, less than 2.5 times its time, on 8^4 sites (the fields' bytes
+    are a third of the operator's) less than 4 times."""
+    g = torch.Generator(device="cuda").manual_seed(12)
+
+    def field(*shape):
+        return torch.randn(shape, generator=g, device="cuda", dtype=torch.complex128)
+
+    dims = (e,) * 4
+    p = _p(3, [(4, 4, 4, 4), (2, 2, 2, 2)], [n, 4], n_inv=0)
+    ctx = dd.create(dims, 1.0, 1.0, 0.3 * field(e, e, e, e, 4, 3, 3))
+    H = dd.build_hierarchy(ctx, to_params(dd, p, dd.F32, half=True), field(n, e, e, e, e, 12))
+    b = field(nb, (e // 4) ** 4, 2 * n).to(torch.complex64)
+    z = torch.zeros_like(b)
+
+    def time(call, k):
+        best = 1e30
+        ev = [torch.cuda.Event(enable_timing=True) for _ in range(2)]
+        for _ in range(8):
+            ev[0].record()
+            for _ in range(20):
+                call(k)
+            ev[1].record()
+            torch.cuda.synchronize()
+            best = min(best, ev[0].elapsed_time(ev[1]) / 20)
+        return best
+
+    for name, call in (("apply", lambda k: dd.apply_Dc(H, 1, b, z, k, dd.F16, dd.NATIVE)),
+                       ("sap", lambda k: dd.sap_smooth(H, 1, b, z, 1, k, dd.F16, dd.NATIVE))):
+        t1, tn = time(call, 1), time(call, nb)
+        say(f"  {name} e={e} d={2 * n}: one field {1e3 * t1:.1f} us, {nb} fields {1e3 * tn:.1f} us")
+        assert tn <= bound * t1
