@@ -88,10 +88,13 @@ class Reducer {
   // scales of a batched call; device slots stay valid for the next 63 calls
   BArg upload(const std::vector<std::complex<double>>& c, const std::vector<double>& scale, int nb,
               hipStream_t s);
+  // n <= HOST_WORDS coherent host words for a caller's kernels (device alias *dev)
+  static constexpr int HOST_WORDS = 8 * NBMAX;
+  void host_words(int** host, int** dev, int n);
  private:
   DevArray<double> partial_;    // [NBMAX][GMAX][2*(KMAX+1)]
   double2* result_ = nullptr;   // [NBMAX][KMAX+1], device alias of host_
-  double2* host_ = nullptr;     // coherent pinned host memory
+  double2* host_ = nullptr;     // coherent pinned host memory, host_words behind the results
   // coefficient ring: pinned staging and device slots, an event per slot
   static constexpr int NSLOT = 64;
   unsigned char* cstage_ = nullptr;

@@ -414,10 +414,15 @@ Reducer::Reducer() {
   // the final sums are written by the kernels straight into coherent pinned
   // host memory: after the stream synchronisation the host reads them with
   // no copy in between
-  DD_CHECK_HIP(hipHostMalloc(&host_, sizeof(double2) * NBMAX * (KMAX + 1), hipHostMallocCoherent));
+  DD_CHECK_HIP(hipHostMalloc(&host_, sizeof(double2) * NBMAX * (KMAX + 1) + sizeof(int) * HOST_WORDS, hipHostMallocCoherent));
   DD_CHECK_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&result_), host_, 0));
   DD_CHECK_HIP(hipHostMalloc(&cstage_, slot * NSLOT, hipHostMallocDefault));
   for (int k = 0; k < NSLOT; ++k) DD_CHECK_HIP(hipEventCreateWithFlags(&cev_[k], hipEventDisableTiming));
+}
+void Reducer::host_words(int** host, int** dev, int n) {
+  DD_REQUIRE(n <= HOST_WORDS, "too many host words");
+  *host = reinterpret_cast<int*>(host_ + NBMAX * (KMAX + 1));
+  *dev = reinterpret_cast<int*>(result_ + NBMAX * (KMAX + 1));
 }
 Reducer::~Reducer() {
   for (int k = 0; k < NSLOT; ++k)

@@ -6,7 +6,8 @@
 // Wilson-clover operator).  A batch of systems advances together with its
 // own scalars and stopping test per system.
 //
-// The scalars stay on the device, so that an iteration is four kernels and no
+// The scalars stay on the device, so that an iteration is four kernels (six
+// where the stencil's norm parts are folded first) and, after the first few, no
 // host round trip:
 //   w = D p and parts of <w, w>;
 //   alpha = gamma / <w, w>, r -= alpha w and parts of <r, r>;
@@ -47,6 +48,12 @@ struct CgSys {
 constexpr int CG_WG = 256;
 constexpr int CG_PARTS = 1024;   // most parts an update's workgroups sum themselves
 constexpr int CG_RING = 4;       // iterations the host runs ahead of the stopping test, plus one
+// Iterations whose stopping test is read before the next is issued: a run of k
+// iterations that the host is ahead of issues k + 2, which a short one (a warm
+// start, a loose tolerance) would not make up for.  A call of one iteration on
+// 8^4 340 us with host scalars, 500 with the host ahead, 330 so; on 32^3x64 9.8,
+// 12.6, 8.2 ms.
+constexpr int CG_EAGER = 8;
 
 // the sum of n parts, the same in every thread and in every workgroup
 __device__ double sum_parts(const double* __restrict__ p, int n, double* lds) {
@@ -95,11 +102,13 @@ __global__ void __launch_bounds__(CG_WG) k_cg_residual(CgSys* __restrict__ sys, 
   if (threadIdx.x == 0) rr[(long long)k * gridDim.x + blockIdx.x] = (lds[0] + lds[1]) + (lds[2] + lds[3]);
 }
 
-// flag (host): whether the system goes on after this iteration
+// flag (host): whether the system goes on after this iteration; count (host):
+// its iterations and status so far
 __global__ void __launch_bounds__(CG_WG) k_cg_direction(CgSys* __restrict__ sys, int cur, const double* __restrict__ rr,
                                                         int nrr, const double* __restrict__ zz, int nzz,
                                                         const double2* __restrict__ z, double2* __restrict__ p,
-                                                        double2* __restrict__ x, long long n, int* __restrict__ flag) {
+                                                        double2* __restrict__ x, long long n, int* __restrict__ flag,
+                                                        int2* __restrict__ count) {
   __shared__ double lds[4];
   const int k = blockIdx.y, was = sys[k].live[cur];
   const double rho = sum_parts(rr + (long long)k * nrr, nrr, lds), gam1 = sum_parts(zz + (long long)k * nzz, nzz, lds);
@@ -112,9 +121,11 @@ __global__ void __launch_bounds__(CG_WG) k_cg_direction(CgSys* __restrict__ sys,
     if (was) {
       ++sys[k].iters;
       if (!live) sys[k].status = finite ? DDAMG_OK : DDAMG_ENONFINITE;
+      count[k] = make_int2(sys[k].iters, sys[k].status);
     }
     flag[k] = live;
   }
+  if (!was) return;   // a system that has ended keeps its iterate
   z += k * n;
   p += k * n;
   x += k * n;
@@ -130,23 +141,17 @@ __global__ void __launch_bounds__(CG_WG) k_cg_direction(CgSys* __restrict__ sys,
   }
 }
 
-// coherent pinned host memory the kernels write their flags to
-struct HostFlags {
-  int* host = nullptr;
-  int* dev = nullptr;
+struct Events {
   hipEvent_t ev[CG_RING] = {};
-  explicit HostFlags(int nb) {
-    DD_CHECK_HIP(hipHostMalloc(&host, sizeof(int) * CG_RING * nb, hipHostMallocCoherent));
-    DD_CHECK_HIP(hipHostGetDevicePointer(reinterpret_cast<void**>(&dev), host, 0));
+  Events() {
     for (auto& e : ev) DD_CHECK_HIP(hipEventCreateWithFlags(&e, hipEventDisableTiming));
   }
-  ~HostFlags() {
+  ~Events() {
     for (auto& e : ev)
       if (e) (void)hipEventDestroy(e);
-    if (host) (void)hipHostFree(host);
   }
-  HostFlags(const HostFlags&) = delete;
-  HostFlags& operator=(const HostFlags&) = delete;
+  Events(const Events&) = delete;
+  Events& operator=(const Events&) = delete;
 };
 
 }  // namespace
@@ -167,17 +172,17 @@ void cgnr(Context& ctx, const double2* b, double2* x, int nb, double tol, int ma
   // they are many, and one per workgroup of the residual update
   const int nd = dslash_norm_parts(g.nblk), np = nd > CG_PARTS ? 1 : nd;
   const int grid = (int)std::min<long long>(CG_PARTS, (n + 4 * CG_WG - 1) / (4 * CG_WG));
-  DevArray<double> dparts, sums, rparts;
-  DevArray<CgSys> sys;
-  dparts.alloc((size_t)nb * nd);
-  sums.alloc(nb);
-  rparts.alloc((size_t)nb * grid);
-  sys.alloc(nb);
-  const double* parts = np == 1 ? sums.p : dparts.p;
+  static_assert(sizeof(CgSys) % sizeof(double) == 0, "the norms follow the systems' records");
+  DevArray<double> small;   // one allocation: a call on a small lattice notices each
+  const size_t sw = sizeof(CgSys) / sizeof(double);
+  small.alloc(nb * (sw + nd + 1 + grid));
+  CgSys* sys = reinterpret_cast<CgSys*>(small.p);
+  double *dparts = small.p + nb * sw, *sums = dparts + (size_t)nb * nd, *rparts = sums + nb;
+  const double* parts = np == 1 ? sums : dparts;
   auto apply = [&](const double2* v, double2* out, bool g5) {
-    dslash_norm(D, v, out, g5, dparts.p, s, nb);
+    dslash_norm(D, v, out, g5, dparts, s, nb);
     if (np == 1) {
-      k_cg_fold<<<nb, CG_WG, 0, s>>>(dparts.p, nd, sums.p);
+      k_cg_fold<<<nb, CG_WG, 0, s>>>(dparts, nd, sums);
       DD_LAUNCH_CHECK();
     }
   };
@@ -203,32 +208,36 @@ void cgnr(Context& ctx, const double2* b, double2* x, int nb, double tol, int ma
     h[k].gamma[0] = gam[k];
     any = any || h[k].live[0];
   }
+  const int2* count = nullptr;   // host words: complete when the stream has drained
   if (any && max_iter > 0) {
-    DD_CHECK_HIP(hipMemcpyAsync(sys.p, h.data(), sizeof(CgSys) * nb, hipMemcpyHostToDevice, s));
-    HostFlags fl(nb);
+    DD_CHECK_HIP(hipMemcpyAsync(sys, h.data(), sizeof(CgSys) * nb, hipMemcpyHostToDevice, s));
+    Events done;
+    int *host = nullptr, *dev = nullptr;
+    red.host_words(&host, &dev, (2 + CG_RING) * nb);
+    count = reinterpret_cast<const int2*>(host);
+    const int* flag_host = host + 2 * nb;
+    int* flag_dev = dev + 2 * nb;
     for (int it = 0; it < max_iter; ++it) {
       const int cur = it & 1, slot = it % CG_RING;
-      // the flags of CG_RING - 1 iterations ago decide whether to go on: the
+      // the flags of `ahead` iterations ago decide whether to go on: the
       // iterations issued past the last system's stopping test change nothing
-      // (alpha = 0)
-      if (it >= CG_RING - 1) {
-        const int old = (it - (CG_RING - 1)) % CG_RING;
-        DD_CHECK_HIP(hipEventSynchronize(fl.ev[old]));
+      const int ahead = it <= CG_EAGER ? 1 : CG_RING - 1;
+      if (it >= ahead) {
+        const int old = (it - ahead) % CG_RING;
+        DD_CHECK_HIP(hipEventSynchronize(done.ev[old]));
         bool more = false;
-        for (int k = 0; k < nb; ++k) more = more || static_cast<volatile int*>(fl.host)[old * nb + k] != 0;
+        for (int k = 0; k < nb; ++k) more = more || static_cast<const volatile int*>(flag_host)[old * nb + k] != 0;
         if (!more) break;
       }
       apply(p.p, w.p, false);
-      k_cg_residual<<<dim3(grid, nb), CG_WG, 0, s>>>(sys.p, cur, parts, np, w.p, r.p, n, rparts.p);
+      k_cg_residual<<<dim3(grid, nb), CG_WG, 0, s>>>(sys, cur, parts, np, w.p, r.p, n, rparts);
       DD_LAUNCH_CHECK();
       apply(r.p, z.p, true);
-      k_cg_direction<<<dim3(grid, nb), CG_WG, 0, s>>>(sys.p, cur, rparts.p, grid, parts, np, z.p, p.p, x, n,
-                                                      fl.dev + slot * nb);
+      k_cg_direction<<<dim3(grid, nb), CG_WG, 0, s>>>(sys, cur, rparts, grid, parts, np, z.p, p.p, x, n,
+                                                      flag_dev + slot * nb, reinterpret_cast<int2*>(dev));
       DD_LAUNCH_CHECK();
-      DD_CHECK_HIP(hipEventRecord(fl.ev[slot], s));
+      DD_CHECK_HIP(hipEventRecord(done.ev[slot], s));
     }
-    DD_CHECK_HIP(hipMemcpyAsync(h.data(), sys.p, sizeof(CgSys) * nb, hipMemcpyDeviceToHost, s));
-    DD_CHECK_HIP(hipStreamSynchronize(s));
   }
   // the true residual of every system
   dslash<double>(D, x, r.p, s, nb);
@@ -236,9 +245,10 @@ void cgnr(Context& ctx, const double2* b, double2* x, int nb, double tol, int ma
   norms2(red, r.p, n, nb, rho, s);
   for (int k = 0; k < nb; ++k) {
     const double rel = bn[k] > 0 ? std::sqrt(std::max(rho[k], 0.0) / bn[k]) : 0.0;
-    st[k].outer_iters = h[k].iters;
+    const int2 c = count && h[k].live[0] ? count[k] : make_int2(0, h[k].status);
+    st[k].outer_iters = c.x;
     st[k].true_relres = rel;
-    st[k].status = h[k].status == DDAMG_OK && !(rel <= tol) ? DDAMG_ENOCONV : h[k].status;
+    st[k].status = c.y == DDAMG_OK && !(rel <= tol) ? DDAMG_ENOCONV : c.y;
   }
 }
 
