@@ -742,7 +742,7 @@ void orthonormalise_coarse(const AggTables& a, const AggDev& ad, int d, int N, l
 // column per workgroup with a wavefront reduction per entry took 5.13 ms.
 // ---------------------------------------------------------------------------
 struct GalFineGeom {
-  int agg[4];
+  int nb[4], agg[4];
 };
 
 // Galerkin grids: workgroup bid of 8 * ceil(nagg / 8) * ncol handles
@@ -957,14 +957,149 @@ __global__ void __launch_bounds__(256) k_self_adjoint(int twoN, double2* __restr
   }
 }
 
+// The same for few test vectors, one column per workgroup and one thread per
+// site: for the column u = P_k restricted to chirality sigma the thread forms in
+// turn the self part (both directions of every hop inside the aggregate) and the
+// four face parts, and projects each on the rows P_k'(x) with a wavefront
+// reduction per entry.  Its work grows with N^2 and its time, where the
+// workgroups do not fill the device, with N; the tiles above take 16 columns'
+// time for any number.
+// y += -1/2 * hop of the column restricted to chirality SIGMA: the other
+// spinor half is a compile-time zero (not loaded), and the factor -1/2 is
+// applied to the input so that the hop accumulates straight into y
+template <int MU, bool FWD, int SIGMA>
+__device__ inline void gal_col_hop(const FineOpView<double>& op, const double2* __restrict__ Pk, int blk, int loc,
+                               double2 y[12]) {
+  constexpr int bit = 1 << MU;
+  int nb;
+  if constexpr (FWD) nb = (loc & bit) ? op.nbr[blk * 8 + 2 * MU] : blk;
+  else nb = (loc & bit) ? blk : op.nbr[blk * 8 + 2 * MU + 1];
+  double2 psi[12], u[9];
+  const double2* p = Pk + (long long)nb * 192 + (loc ^ bit);
+#pragma unroll
+  for (int c = 0; c < 12; ++c)
+    psi[c] = (c / 6) == SIGMA ? cscale(p[c * 16], -0.5) : czero<double>();
+  if constexpr (FWD) load_link<double, MU>(op.U, blk, loc, u);
+  else load_link<double, MU>(op.U, nb, loc ^ bit, u);
+  hop_apply<double, MU, FWD>(psi, u, y);
+}
+
+template <int MU, int SIGMA>
+__device__ inline void gal_col_hops(const FineOpView<double>& op, const double2* Pk, int blk, int loc,
+                                       const bool* fin, const bool* bin, double2 y[12]) {
+  if (fin[MU]) gal_col_hop<MU, true, SIGMA>(op, Pk, blk, loc, y);
+  if (bin[MU]) gal_col_hop<MU, false, SIGMA>(op, Pk, blk, loc, y);
+}
+
+// part tau of the column (SIGMA, k) at this thread's site: tau = 0 the self
+// part (clover and the hops inside the aggregate), tau = 1 + mu the forward
+// face part across the +mu face
+template <int SIGMA>
+__device__ inline void gal_col_part(const FineOpView<double>& op, const double2* __restrict__ Pk, int blk, int loc,
+                                const bool* fin, const bool* bin, int tau, double2 y[12]) {
+  if (tau == 0) {
+    // the clover is block diagonal in chirality: only block SIGMA acts
+    double2 u[6];
+    const double2* p = Pk + (long long)blk * 192 + loc + 6 * SIGMA * 16;
+#pragma unroll
+    for (int c = 0; c < 6; ++c) u[c] = p[c * 16];
+#pragma unroll
+    for (int c = 0; c < 6; ++c) y[6 * (1 - SIGMA) + c] = czero<double>();
+    const double2* a = op.A + (long long)blk * 576 + loc;
+    clover_block<double>(SIGMA, [&](int e) { return a[e * 16]; }, u, y + 6 * SIGMA);
+    gal_col_hops<0, SIGMA>(op, Pk, blk, loc, fin, bin, y);
+    gal_col_hops<1, SIGMA>(op, Pk, blk, loc, fin, bin, y);
+    gal_col_hops<2, SIGMA>(op, Pk, blk, loc, fin, bin, y);
+    gal_col_hops<3, SIGMA>(op, Pk, blk, loc, fin, bin, y);
+  } else {
+#pragma unroll
+    for (int c = 0; c < 12; ++c) y[c] = czero<double>();
+    const int mu = tau - 1;
+    if (!fin[mu]) {
+      if (mu == 0) gal_col_hop<0, true, SIGMA>(op, Pk, blk, loc, y);
+      else if (mu == 1) gal_col_hop<1, true, SIGMA>(op, Pk, blk, loc, y);
+      else if (mu == 2) gal_col_hop<2, true, SIGMA>(op, Pk, blk, loc, y);
+      else gal_col_hop<3, true, SIGMA>(op, Pk, blk, loc, y);
+    }
+  }
+}
+
+__global__ void __launch_bounds__(256) k_galerkin_fine_cols(GalFineGeom gg, const int* __restrict__ members,
+                                                       int nbpa, int N, int nagg, FineOpView<double> op,
+                                                       const double2* __restrict__ P, long long fstride,
+                                                       double2* __restrict__ Dc) {
+  __shared__ double red[4 * NMAX * 4];
+  int A, col;
+  if (!agg_col_xcd(blockIdx.x, nagg, 2 * N, A, col)) return;
+  const int sigma = col / N, k = col % N;
+  const int t = threadIdx.x;
+  const int blk = members[A * nbpa + (t >> 4)], loc = t & 15;
+  // fine coordinates -> which hops stay inside the aggregate
+  bool fin[4], bin[4];
+  {
+    int bcs[4];
+    block_decode(gg.nb, blk, bcs);
+    for (int mu = 0; mu < 4; ++mu) {
+      const int bc = bcs[mu];
+      const int x = 2 * bc + ((loc >> mu) & 1);
+      const int xm = x % gg.agg[mu];
+      fin[mu] = xm != gg.agg[mu] - 1;
+      bin[mu] = xm != 0;
+    }
+  }
+  const double2* Pk = P + k * fstride;
+  const int twoN = 2 * N;
+#pragma unroll 1
+  for (int tau = 0; tau < 5; ++tau) {
+    double2 y[12];
+    if (sigma == 0) gal_col_part<0>(op, Pk, blk, loc, fin, bin, tau, y);
+    else gal_col_part<1>(op, Pk, blk, loc, fin, bin, tau, y);
+    // a face part is nonzero only on the aggregate's face sites: the other
+    // threads skip the loads of the rows of P and contribute zeros
+    const bool live = tau == 0 || !fin[tau - 1];
+#pragma unroll 2
+    for (int kp = 0; kp < N; ++kp) {
+      double2 p0 = czero<double>(), p1 = czero<double>();
+      if (live) {
+        double2 w[12];
+        load_spinor<double>(P + kp * fstride, blk, loc, w);
+#pragma unroll
+        for (int c = 0; c < 6; ++c) {
+          cjfma(p0, w[c], y[c]);
+          cjfma(p1, w[6 + c], y[6 + c]);
+        }
+      }
+      stash4<double>(red, N, kp, p0.x, p0.y, p1.x, p1.y);
+    }
+    __syncthreads();
+    if (t < twoN)
+      Dc[(((long long)A * 5 + tau) * twoN + t) * twoN + col] = collect<double>(red, N, t / N, t % N);
+    __syncthreads();
+  }
+}
+
+// Which of the two takes N test vectors on nagg aggregates.  Import of the vectors,
+// P and D_c (with the orthonormalisation) in us, tiles / columns: N = 2 369 / 208
+// on 16 aggregates, 408 / 273 on 256, 737 / 447 on 512; N = 5 519 / 502, 905 / 857,
+// 1770 / 1656 on 256, 512, 1024; N = 6 551 / 589, 977 / 1040, 1924 / 2041; N = 8 544
+// / 347 on 16, 835 / 715 on 64, 635 / 806 on 256; N = 10 1007 / 946 on 64, 565 /
+// 641 on 128; N = 20 1124 / 1035 on 16, 1400 / 1436 on 32, 2207 / 2527 on 64; N =
+// 28 1668 / 1712 on 16.
+inline bool gal_by_columns(int N, int nagg) { return N <= 5 || (N <= 24 && (long long)N * nagg <= 640); }
+
 void galerkin_fine(const FineGeom& g, const AggTables& a, const AggDev& ad, int N,
                    const FineOpView<double>& op, const double2* P, double2* Dc, hipStream_t s) {
   DD_REQUIRE(a.asz == 256, "fine Galerkin kernel expects aggregates of 256 sites");
   DD_REQUIRE(N >= 1 && N <= NMAX, "too many test vectors");
   GalFineGeom gg;
-  for (int mu = 0; mu < 4; ++mu) gg.agg[mu] = a.agg[mu];
+  for (int mu = 0; mu < 4; ++mu) gg.nb[mu] = g.nb[mu], gg.agg[mu] = a.agg[mu];
   const unsigned grid = agg_col_grid(a.nagg, (2 * N + 15) / 16);
   const long long fs = (long long)g.nblk * 192;
+  if (gal_by_columns(N, a.nagg)) {
+    k_galerkin_fine_cols<<<agg_col_grid(a.nagg, 2 * N), 256, 0, s>>>(gg, ad.members, a.asz / 16, N, a.nagg, op, P, fs, Dc);
+    DD_LAUNCH_CHECK();
+    return;
+  }
   if (N <= 16) k_galerkin_fine<1><<<grid, 512, 0, s>>>(gg, ad.members, N, a.nagg, op, P, fs, Dc);
   else k_galerkin_fine<2><<<grid, 512, 0, s>>>(gg, ad.members, N, a.nagg, op, P, fs, Dc);
   k_self_adjoint<<<a.nagg, 256, 0, s>>>(2 * N, Dc);

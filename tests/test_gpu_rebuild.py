@@ -8,14 +8,17 @@ Tolerance 1e-12 relative, as for the other FP64 setup products: sums of at
 most 3072 products in FP64 (sqrt(3072) 2^-53 = 6e-15) after an
 orthonormalisation whose conditioning for random vectors costs a digit or
 two."""
+import time
+
 import numpy as np
 import pytest
+import torch
 
 import workloads as W
 from oracle.aggregation import Aggregation
 from oracle.dirac import WilsonClover
 from oracle.galerkin import galerkin
-from tests.gpu_util import dev, export_Dc, export_P, oracle_from_gpu, relerr, say, to_params
+from tests.gpu_util import dev, empty, export_Dc, export_P, host, oracle_from_gpu, relerr, say, to_params
 from tests.test_gpu_hierarchy import _p
 
 pytestmark = pytest.mark.gpu
@@ -65,3 +68,52 @@ def test_rebuild_coarse(dd, n0, n1):
     assert relerr(export_P(dd, H, 1, n1), A.columns()) <= TOL
     OH = oracle_from_gpu(dd, H, WilsonClover(U, -0.3, 1.0), p)
     assert relerr(export_Dc(dd, H, 2), _blocks(galerkin(OH.ops[1], A))) <= TOL
+
+
+# more aggregates: the tiles take N >= 6 here, the one-column kernel N = 5, each
+# on aggregates that are not 4^4 too
+@pytest.mark.parametrize("agg,n", [((4, 4, 4, 4), 5), ((8, 4, 4, 2), 5), ((4, 4, 4, 4), 6), ((8, 4, 4, 2), 13),
+                                   ((4, 2, 8, 4), 16), ((2, 4, 4, 8), 17), ((4, 4, 4, 4), 24)])
+def test_rebuild_fine_products(dd, agg, n):
+    """D_c x = P^H D P x with the library's own P and D in FP64, on 256 aggregates."""
+    dims = (16, 16, 16, 16)
+    say(f"rebuild products agg={agg} N={n}")
+    U, tv = W.links(dims, 0.5, 61), dev(W.test_vectors(dims, 12, n, 62))
+    ctx = dd.create(dims, -0.3, 1.0, dev(U))
+    H = dd.build_hierarchy(ctx, to_params(dd, _p(2, [agg], [n], n_inv=0)), tv)
+    dd.import_test_vectors(H, 0, tv)
+    cdims, _ = dd.level_info(H, 1)
+    x = dev(W.gaussian_field(cdims, 2 * n, 67, nrhs=2))
+    fine, df = (empty((2,) + tuple(dims[::-1]) + (12,)) for _ in range(2))
+    fine.zero_()
+    dd.prolong(H, 0, x, fine, nrhs=2)
+    dd.apply_D(ctx, fine, df, nrhs=2)
+    ref, out = empty(tuple(x.shape)), empty(tuple(x.shape))
+    dd.restrict(H, 0, df, ref, nrhs=2)
+    dd.apply_Dc(H, 1, x, out, nrhs=2)
+    e = relerr(host(out), host(ref))
+    say(f"  relerr {e:.2e}")
+    assert e <= TOL
+
+
+def test_rebuild_few_vectors_time(dd):
+    """One vector costs a fraction of sixteen (a tile's columns are not paid for):
+    less than 0.21 of the time on 16^3x32."""
+    dims = (16, 16, 16, 32)
+    g = torch.Generator(device="cuda").manual_seed(9)
+    ctx = dd.create(dims, 1.0, 1.0, 0.3 * torch.randn(dims[::-1] + (4, 3, 3), generator=g, device="cuda",
+                                                      dtype=torch.complex128))
+    t = {}
+    for n in (1, 16):
+        tv = torch.randn((n,) + dims[::-1] + (12,), generator=g, device="cuda", dtype=torch.complex128)
+        H = dd.build_hierarchy(ctx, to_params(dd, _p(2, [(4, 4, 4, 4)], [n], n_inv=0)), tv)
+        t[n] = 1e30
+        for _ in range(8):
+            torch.cuda.synchronize()
+            t0 = time.perf_counter()
+            for _ in range(5):
+                dd.import_test_vectors(H, 0, tv)
+            torch.cuda.synchronize()
+            t[n] = min(t[n], (time.perf_counter() - t0) / 5)
+    say(f"rebuild 16^3x32: N = 1 {1e6 * t[1]:.0f} us, N = 16 {1e6 * t[16]:.0f} us")
+    assert t[1] <= 0.21 * t[16]
