@@ -74,7 +74,7 @@ template <typename T> C<T>* scratch(DevArray<double2>& a, size_t n) {
   }
   return reinterpret_cast<C<T>*>(a.p);
 }
-template <typename T> C<T>* ctx_scratch(Context& c, int w, size_t n) { return scratch<T>(w ? c.s64b : c.s64a, n); }
+template <typename T> C<T>* ctx_scratch(Context& c, size_t n) { return scratch<T>(c.s64a, n); }
 template <typename T> C<T>* hier_scratch(Hierarchy& h, int w, size_t n) { return scratch<T>(w ? h.sc64b : h.sc64a, n); }
 
 // canonical complex128 <-> native at T for nrhs level-l fields (n complex each)
@@ -90,8 +90,8 @@ void from_nat(Context& c, int l, long long n, int nrhs, const C<T>* in, double2*
 }
 
 // Every entry point hands the whole batch of nrhs fields to one batched
-// call; with the canonical layout the batch is converted through scratch
-// fields first.
+// call; with the canonical layout the stencil reads and writes the canonical
+// fields, the other calls convert the batch through scratch fields.
 template <typename T, bool HALF = false>
 void apply_D_impl(Context& c, const void* in, void* out, int nrhs, int layout, hipStream_t s) {
   const auto op = [&] {
@@ -410,7 +410,7 @@ int ddamg_to_native(ddamg_ctx ctx, ddamg_hier hier, int level, const void* in, v
     const WorkspaceScope wsc(c.ws.get());
     if (prec == DDAMG_F16S) {
       const long long n = c.g.V * 12;
-      double2* a = ctx_scratch<double>(c, 0, n * nrhs);
+      double2* a = ctx_scratch<double>(c, n * nrhs);
       fine_to_native<double>(c.g, static_cast<const double2*>(in), a, nrhs, s);
       const HsPacked po = hs_packed(out, n, nrhs);
       encode_h<double>(c.g, a, po.h, po.s, nrhs, s);
@@ -438,7 +438,7 @@ int ddamg_from_native(ddamg_ctx ctx, ddamg_hier hier, int level, const void* in,
     const WorkspaceScope wsc(c.ws.get());
     if (prec == DDAMG_F16S) {
       const long long n = c.g.V * 12;
-      double2* a = ctx_scratch<double>(c, 0, n * nrhs);
+      double2* a = ctx_scratch<double>(c, n * nrhs);
       const HsPacked pi = hs_packed(in, n, nrhs);
       decode_h<double>(c.g, pi.h, pi.s, a, nrhs, s);
       fine_from_native<double>(c.g, a, static_cast<double2*>(out), nrhs, s);

@@ -31,7 +31,8 @@ struct Context {
   DevArray<__half2> U16, A16;     // FP16 storage, made on first request
   bool half_ready = false;
   DevArray<int> nbr, cblk;
-  // scratch for canonical-layout calls, raw bytes shared by both precisions
+  // scratch for conversions (s64a); s64b is only carved from a caller's
+  // workspace, whose size counts two fields per right-hand side
   DevArray<double2> s64a, s64b;
   template <typename T> FineOpView<T> view() const;
   FineOpView<float, __half2> view16() const { return {U16.p, A16.p, nbr.p, g.nblk}; }

@@ -91,8 +91,8 @@ static void check_lattice(const ddamg_lattice* lat) {
 }
 
 // geometry, neighbour tables and the operator arrays of a context (no
-// kernels); with a workspace also the FP16 copies and the canonical-layout
-// scratch that would otherwise be made on first use
+// kernels); with a workspace also the FP16 copies and the conversion scratch
+// that would otherwise be made on first use
 static void context_layout(Context& c, const ddamg_lattice* lat, bool half, int nrhs_max, hipStream_t s) {
   c.g = make_fine_geom(lat->dims);
   c.m0 = lat->m0;

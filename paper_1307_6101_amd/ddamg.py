@@ -277,8 +277,8 @@ def apply_D(ctx, inp, out, nrhs=1, prec=F64, layout=CANONICAL):
 
 
 def apply_D_noalloc(ctx, inp, out, nrhs=1, prec=F64):
-    """ddamg_apply_D_noalloc: canonical out = D inp through the library's
-    fixed device staging array (no allocation)."""
+    """ddamg_apply_D_noalloc: canonical out = D inp without an allocation or
+    staging memory."""
     _check(load_library().ddamg_apply_D_noalloc(ctx.handle, _ptr(inp), _ptr(out), nrhs, prec, _stream()))
 
 

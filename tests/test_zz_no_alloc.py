@@ -55,3 +55,33 @@ def test_noalloc_size_limit(dd):
     assert ei.value.status == dd.EINVAL and "staging" in str(ei.value)
     dd.apply_D_noalloc(ctx, x[:1], y[:1], nrhs=1, prec=dd.F64)
     torch.cuda.synchronize()
+
+
+def test_noalloc_streams(dd):
+    """Calls that overlap on two streams keep their results apart, and a captured
+    call replays."""
+    dims = (8, 8, 16, 16)
+    ctx = dd.create(dims, -0.3, 1.0, dev(W.links(dims, 0.5, 7300)))
+    xs = [dev(W.gaussian_spinor(dims, 7310 + k, nrhs=4)) for k in range(8)]
+    refs = [torch.empty_like(x) for x in xs]
+    for x, r in zip(xs, refs):
+        dd.apply_D(ctx, x, r, nrhs=4)
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [torch.zeros_like(x) for x in xs]
+    torch.cuda.synchronize()
+    for _ in range(10):
+        for k, (x, o) in enumerate(zip(xs, outs)):
+            with torch.cuda.stream(streams[k % 2]):
+                dd.apply_D_noalloc(ctx, x, o, nrhs=4)
+    torch.cuda.synchronize()
+    assert all(torch.equal(o, r) for o, r in zip(outs, refs))
+    x, o = xs[0].clone(), torch.zeros_like(xs[0])
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        dd.apply_D_noalloc(ctx, x, o, nrhs=4)
+    for k in range(3):
+        x.copy_(xs[k])
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(o, refs[k]), k
