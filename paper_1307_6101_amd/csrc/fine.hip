@@ -456,7 +456,7 @@ __global__ void __launch_bounds__(256) k_dslash(FineOpView<T, S> op, const V* __
                                                 const float* __restrict__ ins, C<T>* __restrict__ out,
                                                 long long fs, int gx, int nb) {
   int x, r;
-  xcd_slab_rhs(blockIdx.x, gx, nb, x, r);
+  xcd_slab_rhs<S>(blockIdx.x, gx, nb, x, r);
   const int tid = x * blockDim.x + threadIdx.x;
   const int blk = tid >> 4, loc = tid & 15;
   if (blk >= op.nblk) return;
@@ -488,7 +488,7 @@ __global__ void __launch_bounds__(256) k_dslash_norm(FineOpView<double> op, cons
                                                      long long fs, int gx, int nb) {
   __shared__ double sums[4];
   int x, r;
-  xcd_slab_rhs(blockIdx.x, gx, nb, x, r);
+  xcd_slab_rhs<double2>(blockIdx.x, gx, nb, x, r);
   const int blk = x * 16 + (threadIdx.x >> 4), loc = threadIdx.x & 15;   // nblk is a multiple of 16
   const long long off = (long long)r * fs;
   double2 o[12];
@@ -533,7 +533,7 @@ __global__ void __launch_bounds__(256) k_dslash_canonical(FineOpView<T, S> op, D
   constexpr int PITCH = 13;
   __shared__ C<T> tile[256 * PITCH];
   int x, r;
-  xcd_slab_rhs(blockIdx.x, gx, nb, x, r);
+  xcd_slab_rhs<S>(blockIdx.x, gx, nb, x, r);
   const int t = threadIdx.x, blk = x * 16 + (t >> 4), loc = t & 15;
   const int nt[4] = {g.nb[0] >> 1, g.nb[1] >> 1, g.nb[2] >> 1, g.nb[3] >> 1};
   int tc[4];
@@ -930,7 +930,7 @@ k_sap_colour(FineOpView<T, S> op, const int* __restrict__ cblk,
   constexpr bool CK = ClKeep<S>::value;
   const int t = threadIdx.x, loc = t & 15, p = (t >> 4) & 1;
   int xw, rw;
-  xcd_slab_rhs(blockIdx.x, gx, nb, xw, rw);
+  xcd_slab_rhs<S>(blockIdx.x, gx, nb, xw, rw);
   b += (long long)rw * fs;
   z += (long long)rw * fs;
   if constexpr (HS) {

@@ -71,16 +71,19 @@ __device__ inline int xcd_slab_index(int bid, int nwg) {
 }
 // The same for a batch of nb fields over a one-dimensional grid of gx * nb
 // workgroups: each XCD takes one slab of blocks and goes through it once per
-// group of XCD_FIELDS fields, running the fields of a group back to back on
-// each block chunk.  The operator data of a chunk is then fetched into that
-// XCD's L2 once per group, while the spinors of few enough fields pass through
-// it between one chunk and its neighbours for the chunks' faces to be still
-// there.  12 fields on 16^3x32, FP32, stencil in us for groups of 1, 2, 3, 4, 6,
-// 12: 258, 183, 174, 168, 166, 166 (inputs in the last-level cache; else 3: 209,
-// 4: 208, 6: 209, 12: 216); five FP32 SAP sweeps (one lane a
-// site): 2157, 1652, 1586, 1554, 1464, 1564.  Sets the workgroup's block-chunk
-// index x and field r.
-constexpr int XCD_FIELDS = 6;
+// group of fields, running the fields of a group back to back on each block
+// chunk.  The operator data (of storage S) of a chunk is then fetched into that
+// XCD's L2 once per group, while the spinors of few enough fields pass through it
+// between one chunk and its neighbours for the chunks' faces to be still there.
+// FP32 and FP16 storage in equal groups of up to XCD_FIELDS, FP64, whose operator
+// weighs as much as its spinors, in one group.  Stencil in us with one group /
+// groups of 9 / of 6 (the last one smaller): FP32, 7 fields of 24^4 319 / 319 /
+// 340, 16 fields of 16^3x32 262 / 234 / 234; FP16, 19 fields of 24^4 787 / 734 /
+// 725; FP64, 7 fields of 24^4 646 / 646 / 697, 13 fields 1183 / 1183 / 1241.
+// A SAP sweep: FP32, 7 fields of 24^4 348 / 348 / 357, 16 of 16^3x32 310 / 310 /
+// 310.  Sets the workgroup's block-chunk index x and field r.
+constexpr int XCD_FIELDS = 9;
+template <typename S>
 __device__ inline void xcd_slab_rhs(int bid, int gx, int nb, int& x, int& r) {
   if (gx % 8 != 0) {
     x = bid % gx;
@@ -88,9 +91,10 @@ __device__ inline void xcd_slab_rhs(int bid, int gx, int nb, int& x, int& r) {
     return;
   }
   const int k = bid >> 3, slab = gx >> 3;
-  const int g = k / (slab * XCD_FIELDS), rem = k - g * slab * XCD_FIELDS, gs = min(XCD_FIELDS, nb - g * XCD_FIELDS);
+  const int ng = sizeof(S) == 16 ? 1 : (nb + XCD_FIELDS - 1) / XCD_FIELDS, f = (nb + ng - 1) / ng;
+  const int g = k / (slab * f), rem = k - g * slab * f, gs = min(f, nb - g * f);
   x = (bid & 7) * slab + rem / gs;
-  r = g * XCD_FIELDS + rem % gs;
+  r = g * f + rem % gs;
 }
 
 // complex stores and loads of data that is not used again before it has left
