@@ -117,3 +117,18 @@ def test_cgnr_short_run_time(dd):
         times[name] = min(dt, times.get(name, 1e30))
     say(f"cgnr one iteration: {1e3 * times['tol']:.2f} ms by tolerance, {1e3 * times['limit']:.2f} ms by limit")
     assert times["tol"] <= 1.25 * times["limit"]
+
+
+def test_cgnr_streamed_operator(dd):
+    """One system on a lattice whose FP64 operator does not fit the last-level
+    cache (it is read past the caches), against its known solution; tolerance as
+    for the many norm parts."""
+    dims = (16, 16, 32, 36)
+    say(f"cgnr dims={dims}, one system")
+    ctx = dd.create(dims, -0.3, 1.0, dev(W.links(dims, 0.5, 91)))
+    zs = dev(W.gaussian_spinor(dims, 92, nrhs=2))[:1].contiguous()
+    b, z = torch.empty_like(zs), torch.zeros_like(zs)
+    dd.apply_D(ctx, zs, b)
+    rc, st = dd.cgnr(ctx, b, z, tol=1e-8)
+    assert rc == dd.OK and st[0]["outer_iters"] > 50 and st[0]["true_relres"] <= 1e-8
+    assert float((z - zs).norm() / zs.norm()) <= 1e-6

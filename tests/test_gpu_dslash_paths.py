@@ -89,3 +89,48 @@ def test_seven_fields_time(dd):
         t[n] = min(t.get(n, 1e30), ev[0].elapsed_time(ev[1]) / 10 / n)
     say(f"  per field: six {1e3 * t[6]:.1f} us, seven {1e3 * t[7]:.1f} us")
     assert t[7] <= 1.045 * t[6]
+
+
+def test_streamed_operator(dd):
+    """One field on 32^4, where the operator data (302 MB in FP16) is read past the
+    caches, gives what it gives in a batch of two, where it is not: stencil on
+    native and canonical fields, two SAP sweeps.  Tolerance: the same operations,
+    at most contracted otherwise: 1e-14 in FP64, 1e-6 in FP32 (FP16 spinors: 4 u_16)."""
+    from tests.gpu_util import to_params
+    from tests.test_gpu_hierarchy import _p
+    dims, V = (32, 32, 32, 32), 32 ** 4
+    ctx, g = _random_context(dd, dims, 43)
+
+    def field(n, dt=torch.complex128):
+        return torch.randn((n, V, 12), generator=g, device="cuda", dtype=dt)
+
+    def same(a, b, tol):
+        assert float((a - b).norm()) <= tol * float(b.norm())
+
+    P = to_params(dd, _p(2, [(4, 4, 4, 4)], [2], n_inv=0), dd.F32, half=True)
+    P.half_spinors = 1
+    H = dd.build_hierarchy(ctx, P, field(2))
+    H32 = dd.build_hierarchy(ctx, to_params(dd, _p(2, [(4, 4, 4, 4)], [2], n_inv=0), dd.F32), field(2))
+    for prec, dt, tol, hier in ((dd.F64, torch.complex128, 1e-14, H), (dd.F32, torch.complex64, 1e-6, H32),
+                                (dd.F16, torch.complex64, 1e-6, H)):
+        say(f"  streamed operator prec={prec}")
+        x = field(2, dt)
+        y, one = torch.zeros_like(x), torch.zeros_like(x[:1])
+        dd.apply_D(ctx, x, y, nrhs=2, prec=prec, layout=dd.NATIVE)
+        dd.apply_D(ctx, x[1:].contiguous(), one, prec=prec, layout=dd.NATIVE)
+        same(one[0], y[1], tol)
+        z = field(2, dt)
+        z1 = z[1:].clone()
+        dd.sap_smooth(hier, 0, x, z, 2, nrhs=2, prec=prec, layout=dd.NATIVE)
+        dd.sap_smooth(hier, 0, x[1:].contiguous(), z1, 2, prec=prec, layout=dd.NATIVE)
+        same(z1[0], z[1], tol)
+        xc = field(2)
+        yc, onec = torch.zeros_like(xc), torch.zeros_like(xc[:1])
+        dd.apply_D(ctx, xc, yc, nrhs=2, prec=prec)
+        dd.apply_D(ctx, xc[1:].contiguous(), onec, prec=prec)
+        same(onec[0], yc[1], tol)
+    bc, zc = field(2), field(2)
+    z1 = zc[1:].clone()
+    dd.sap_smooth(H, 0, bc, zc, 2, nrhs=2, prec=dd.F16S)
+    dd.sap_smooth(H, 0, bc[1:].contiguous(), z1, 2, prec=dd.F16S)
+    same(z1[0], zc[1], 4 * 2.0 ** -11)
