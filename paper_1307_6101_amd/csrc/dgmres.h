@@ -67,7 +67,7 @@ void gm_solve(const DevGmres& d, int m, int nb, hipStream_t s);
 // The same steps with their vector work for short vectors (those that a
 // workgroup holds in LDS: gm_short), one workgroup per system and one launch
 // each; flag[1 + r] as flag[0] above, per system.  Fields n apart, basis
-// vectors vs apart.
+// vectors vs apart.  They are not slower up to the LDS limit (see dgmres.hip).
 constexpr long long GM_LDS = 53248;
 template <typename T> inline bool gm_short(long long n) { return n * (long long)sizeof(C<T>) <= GM_LDS; }
 // the norm of r0, gm_begin, V_0 = scale r0

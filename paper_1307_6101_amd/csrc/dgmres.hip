@@ -1,6 +1,7 @@
 // Device-side Krylov scalars of the batched GMRES (declarations and the
-// algorithm in dgmres.h).  Every kernel runs one wavefront; lane r serves
-// system r of the batch.
+// algorithm in dgmres.h).  The kernels of the scalars alone run one wavefront
+// whose lane r serves system r of the batch; the fused steps for short vectors
+// run one workgroup per system.
 #include "dgmres.h"
 
 namespace ddamg {
@@ -172,7 +173,9 @@ __global__ void k_gm_solve(DevGmres d, int m, int nb) {
 // costs one wavefront reduction.  A step (norms, Gram-Schmidt twice, Givens
 // rotation, next basis vector) in one launch of 10.7 us on average (1280 FP32
 // components) instead of five: with the wavefront-per-value second reduction
-// pass a solve on 16^3x32 takes 13.3 ms instead of 15.0.
+// pass a solve on 16^3x32 takes 13.3 ms instead of 15.0.  A whole cycle of 24
+// steps (FP32), separate launches / fused: 640 components 1230 / 720 us, 2560
+// 1260 / 930, 6400 1610 / 1590; 32 systems 3200 / 1910, 3270 / 2390, 4770 / 4290.
 // ---------------------------------------------------------------------------
 constexpr int GM_WG = 512, GM_W = GM_WG / 64;
 

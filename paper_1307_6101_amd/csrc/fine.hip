@@ -334,9 +334,8 @@ __device__ inline Nbr8 load_nbr8(const int* __restrict__ nbr, int blk) {
 
 // Completes the arithmetic that produces acc before the statements that
 // follow (empty asm statements that read and write it), so that the next
-// direction's loads are not all issued ahead of it: hoisting the eight hops'
-// loads would need more registers than the colour pass can hold at two
-// wavefronts per SIMD.
+// hop's loads are not issued ahead of it: those of all eight hops on canonical
+// fields would need more registers than two wavefronts per SIMD have.
 template <typename T> __device__ inline void pin12(C<T> (&acc)[12]) {
 #pragma unroll
   for (int c = 0; c < 12; ++c) asm volatile("" : "+v"(acc[c].x), "+v"(acc[c].y));
@@ -908,17 +907,16 @@ template <> struct ClKeep<__half2> : std::true_type {};
 // Bound by its vector instructions on batches (about 2500 a lane, two lanes a
 // site, at three waves per SIMD; one lane a site: 4335 at two), by memory for
 // one field of a large lattice, by latency on a small one, where the two lanes
-// double the wavefronts.  Five
-// sweeps, one lane a site in workgroups of four wavefronts / of one / this:
+// double the wavefronts.  Five sweeps, one lane a site in workgroups of four wavefronts / of one / this:
 // 32^3x64 FP16 operators 2264 / 2128 / 1915 us; 16^3x32 x 12 FP32 fields 1496 /
 // 1410 / 1358; per pass, 12 FP16 fields of 24^3x48 682 / 666 / 667, one FP32
 // field of 16^3x32 24.5 / 22.9 / 19.5; FP64 (two sweeps, 5 fields) - / 650 / 543.
 // Held to three waves per SIMD in FP32 (two: FP16 12-field pass 718).
 //
 // What is read once in a pass (b) goes past the caches, and with NT (op_streams)
-// the result and the clover that is kept too: one field on 32^3x64 with
-// FP16 operators 2334 -> 2257 us for five sweeps, in FP32 3579 -> 3481 us (a
-// batch's z is found again in the last-level cache: 1469 -> 1553 us if not).
+// the result and the clover that is kept too: two sweeps on one field of 32^4
+// with FP16 operators 375 -> 360 us, of 32^3x64 779 -> 752 (a batch's z is found
+// again in the last-level cache: 4 fields of 24^4 413 us, 439 if not).
 template <typename T, typename S, typename V, bool NT>
 __global__ void __launch_bounds__(SAP_WG, sizeof(T) == 8 ? 2 : 3)
 k_sap_colour(FineOpView<T, S> op, const int* __restrict__ cblk,

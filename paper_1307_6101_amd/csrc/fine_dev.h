@@ -123,11 +123,11 @@ __device__ inline __half2 load_nt(const __half2* p) {
   return __builtin_bit_cast(__half2, __builtin_nontemporal_load(reinterpret_cast<const float*>(p)));
 }
 
-template <typename T, typename S = C<T>, bool NT = false>
+template <typename T, typename S = C<T>>
 __device__ inline void load_spinor(const S* __restrict__ f, int blk, int loc, C<T> v[12]) {
   const S* p = f + (long long)blk * 192 + loc;
 #pragma unroll
-  for (int c = 0; c < 12; ++c) v[c] = ldc<T, S>(NT ? load_nt(p + c * 16) : p[c * 16]);
+  for (int c = 0; c < 12; ++c) v[c] = ldc<T, S>(p[c * 16]);
 }
 // A fine spinor field of storage V: complex numbers of the arithmetic
 // precision (V = C<T>), or FP16 (V = __half2), each site's 12 components
@@ -135,10 +135,10 @@ __device__ inline void load_spinor(const S* __restrict__ f, int blk, int loc, C<
 // ([field][nblk * 16], native site order) next to them.  load_site /
 // store_site read and write one site in either form; the scale pointer is
 // not used for V = C<T>.
-template <typename T, typename V, bool NT = false>
+template <typename T, typename V>
 __device__ inline void load_site(const V* __restrict__ f, const float* __restrict__ sc, int blk, int loc,
                                  C<T> v[12]) {
-  load_spinor<T, V, NT>(f, blk, loc, v);
+  load_spinor<T, V>(f, blk, loc, v);
   if constexpr (std::is_same<V, __half2>::value) {
     const T m = sc[(long long)blk * 16 + loc];
 #pragma unroll
@@ -148,7 +148,7 @@ __device__ inline void load_site(const V* __restrict__ f, const float* __restric
     }
   }
 }
-template <typename T, typename V, bool NT = false>
+template <typename T, typename V>
 __device__ inline void store_site(V* __restrict__ f, float* __restrict__ sc, int blk, int loc, const C<T> v[12]) {
   V* p = f + (long long)blk * 192 + loc;
   if constexpr (std::is_same<V, __half2>::value) {
@@ -158,17 +158,10 @@ __device__ inline void store_site(V* __restrict__ f, float* __restrict__ sc, int
     const float inv = m > 0.f ? 1.f / m : 0.f;
     sc[(long long)blk * 16 + loc] = m;
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      const __half2 h = __floats2half2_rn((float)v[c].x * inv, (float)v[c].y * inv);
-      if constexpr (NT) store_nt(p + c * 16, h);
-      else p[c * 16] = h;
-    }
+    for (int c = 0; c < 12; ++c) p[c * 16] = __floats2half2_rn((float)v[c].x * inv, (float)v[c].y * inv);
   } else {
 #pragma unroll
-    for (int c = 0; c < 12; ++c) {
-      if constexpr (NT) store_nt(p + c * 16, v[c]);
-      else p[c * 16] = v[c];
-    }
+    for (int c = 0; c < 12; ++c) p[c * 16] = v[c];
   }
 }
 
