@@ -319,7 +319,7 @@ __global__ void __launch_bounds__(64 * G * ((NJ + 3) / 4), 4) k_capply_mfma(Coar
   in += off;
   out += off;
   const int nr = min(per, nb - (int)blockIdx.y * per);
-  const int kk = lane >> 4, rl = min(lane & 15, nr - 1), g = w / nmt, mt = w - g * nmt;
+  const int kk = lane >> 4, rl = min(lane & 15, nr - 1), g = G > 1 ? w / nmt : 0, mt = w - g * nmt;
   MfmaRows<S, NJ, G> mr;
   mfma_stage<std::is_same<S, __half2>::value, NJ>(
       lds_b, pitch, 0x1FFu, op.nbr9 + (size_t)site * 9, w, nmt * G, lane, d, nr,
@@ -394,7 +394,7 @@ __global__ void __launch_bounds__(64 * G * ((NJ + 3) / 4), 4) k_sap_q_mfma(Coars
   part_prev += poff;
   part_cur += poff;
   const int nr = min(per, nb - (int)blockIdx.y * per);
-  const int kk = lane >> 4, rl = min(lane & 15, nr - 1), g = w / nmt, mt = w - g * nmt;
+  const int kk = lane >> 4, rl = min(lane & 15, nr - 1), g = G > 1 ? w / nmt : 0, mt = w - g * nmt;
   const int pos = pos0 + x, blk = pos / tb.bs;
   const unsigned mask = __builtin_amdgcn_readfirstlane(tb.inmask[pos]);
   MfmaRows<S, NJ, G> mr;
@@ -435,24 +435,25 @@ __global__ void __launch_bounds__(64 * G * ((NJ + 3) / 4), 4) k_sap_q_mfma(Coars
   __syncthreads();
   f32x4 cr, ci;
   mr.apply(lds_b, pitch, rl, cr, ci);
-  // the new residual of the tile's rows, from its parts' sources or the B tile
-  float2 rho[4];
-  if (g == 0)
-    mfma_rows(mt, lane, d, [&](int v, int i) {
-      if constexpr (H) rho[v] = step > 0 ? csub(rown[v], cmul(alpha_s[rl], qown[v])) : rown[v];
-      else rho[v] = lds_b[i * pitch + rl];
-    });
+  // (FP32 storage: the tile's rows of the new residual, before the join takes the B tile's place)
+  float2 keep[4];
+  if constexpr (!H && G > 1)
+    if (g == 0) mfma_rows(mt, lane, d, [&](int v, int i) { keep[v] = lds_b[i * pitch + rl]; });
   mfma_join<G>(lds_b, mt, nmt, g, lane, cr, ci);
   if (g == 0) {
     float a0 = 0.f, a1 = 0.f, a2 = 0.f;
     const bool live = (lane & 15) < nr;
     mfma_rows(mt, lane, d, [&](int v, int i) {
+      float2 rho;
+      if constexpr (H) rho = step > 0 ? csub(rown[v], cmul(alpha_s[rl], qown[v])) : rown[v];
+      else if constexpr (G > 1) rho = keep[v];
+      else rho = lds_b[i * pitch + rl];
       const float2 q = make_float2(cr[v], ci[v]);
-      a0 = rfma(q.x, rho[v].x, rfma(q.y, rho[v].y, a0));
-      a1 = rfma(q.x, rho[v].y, rfma(-q.y, rho[v].x, a1));
+      a0 = rfma(q.x, rho.x, rfma(q.y, rho.y, a0));
+      a1 = rfma(q.x, rho.y, rfma(-q.y, rho.x, a1));
       a2 = rfma(q.x, q.x, rfma(q.y, q.y, a2));
       if (live) {
-        rho_cur[own + i] = rho[v];
+        rho_cur[own + i] = rho;
         q_cur[own + i] = q;
         if (step > 0) {
           cfma(zown[v], alpha_s[rl], rown[v]);
