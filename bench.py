@@ -35,6 +35,8 @@ sys.path.insert(0, ROOT)
 T_START = time.time()
 HBM_PEAK_GBS = 8000.0
 MFMA_F32_PEAK_TFLOPS = 157.3
+# dense FP16: 256 CUs x 4096 flop per cycle x 2.4 GHz
+MFMA_F16_PEAK_TFLOPS = 2516.6
 BATCH_RHS = 12          # batch size of the batched-kernel timings (the 12 spin-colour sources)
 # HBM traffic per launch of the FP32 stencil on the 16^3x32 lattice: None,
 # the kernel's arithmetic has changed since the FETCH_SIZE / WRITE_SIZE runs
@@ -43,9 +45,9 @@ DSLASH_F32_TRAFFIC_BYTES = None
 # HBM traffic per launch of the SAP colour pass on FP16-stored links and
 # clover on the 48^3x96 lattice, from the FETCH_SIZE / WRITE_SIZE counter
 # runs summarised in profiles/ (None until taken for the current kernel)
-SAP_F16_PASS_TRAFFIC_BYTES = 5.572e9
+SAP_F16_PASS_TRAFFIC_BYTES = 5.049e9
 # the same for the pass on FP16 spinors (b, z with one FP32 scale per site)
-SAP_F16S_PASS_TRAFFIC_BYTES = 4.122e9
+SAP_F16S_PASS_TRAFFIC_BYTES = 4.135e9
 # FP32 vector peak without packed FP32 instructions (which the library does
 # not emit): 256 CUs x 64 lanes x 2 flop (FMA) x 2.4 GHz
 VALU_F32_PEAK_TFLOPS = 78.6
@@ -673,9 +675,10 @@ def headline_workload(args, dd, W, np, torch):
                                                     layout=dd.NATIVE), reps)
     flops = 9 * cd * cd * 8 * BATCH_RHS * cV
     cbb = (9 * cd * cd * 4 + 2 * BATCH_RHS * cd * 8) * cV
+    # (on FP16 storage the inputs enter the FP16 matrix cores in two parts)
     kern[f"coarse_apply_mfma_f16store_x{BATCH_RHS}"] = dict(
         seconds=t_cb, algorithmic_bytes=cbb, gbs=cbb / t_cb / 1e9, tflops=flops / t_cb / 1e12,
-        mfma_frac=flops / t_cb / 1e12 / MFMA_F32_PEAK_TFLOPS)
+        mfma_frac=2 * flops / t_cb / 1e12 / MFMA_F16_PEAK_TFLOPS)
     del cin, cout
     for k, v in kern.items():
         ext = f", {v['tflops']:.1f} TFLOP/s" if "tflops" in v else ""
