@@ -106,11 +106,11 @@ struct MfmaRows {
 // ones and sum the exact products in FP32, so the operator enters as it is
 // stored and an input vector x in two FP16 parts of a common power of two per
 // (block, right-hand side), hi = fp16(x s) and mid = fp16(2^11 (x s - hi)):
-// together 23 bits of x, to one unit in its last FP32 place, and no entry by more
-// than 2^-50 of the largest of its (block, right-hand side) (see split_row).  A lane's four
-// columns t, each (re, im), are eight consecutive k of v_mfma_f32_16x16x32_f16
-// in both operands: lane l supplies A[l % 16][8 (l / 16) ..] and B[8 (l / 16)
-// ..][l % 16], the result as for the FP32 instruction.  The real part's B holds
+// together 23 bits of x, one unit in its last FP32 place, and entries far below
+// the largest of their (block, right-hand side) to 2^-50 of that (see split_row).
+// A lane's four columns t, each (re, im), are eight consecutive k of
+// v_mfma_f32_16x16x32_f16 in both operands: lane l supplies A[l % 16][8 (l / 16)
+// ..] and B[8 (l / 16) ..][l % 16], the result as for the FP32 instruction.  The real part's B holds
 // (re, -im), the imaginary part's (im, re).  Error against 64 bits of five SAP
 // sweeps, vector kernels / FP32 products / this: d = 16 1.71e-7 / 1.36e-7 /
 // 1.10e-7, d = 40 2.64e-7 / 1.96e-7 / 1.28e-7, d = 64 3.37e-7 / 2.43e-7 /
@@ -217,7 +217,7 @@ __device__ __forceinline__ uint2 split_row(float2 f, float& inv) {
 }
 
 // Stages the input vectors of a site: row (k, r), slot k of the mask and
-// right-hand side r, is a contiguous read of LR lanes (16, 32 or 64, as d needs),
+// right-hand side r, is a contiguous read of LR lanes (8 to 64, as d needs),
 // so that a wavefront reads 64 / LR right-hand sides of a slot at once, U such
 // reads in flight at a time; get(r, o) loads element o of right-hand side r,
 // fin(r, v) turns what was loaded into the staged value, and mid() runs once

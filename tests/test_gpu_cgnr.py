@@ -2,6 +2,7 @@
 count up to rounding, solutions agreeing to the tolerance's scale, the
 residual bound met with the oracle's operator; a batch equals its systems
 solved alone; the iteration limit and a zero right-hand side."""
+import gc
 import time
 
 import numpy as np
@@ -21,6 +22,15 @@ def dd():
     from paper_1307_6101_amd import ddamg
     ddamg.load_library()
     return ddamg
+
+
+@pytest.fixture(autouse=True)
+def _release():
+    """The library allocates beside torch: what torch keeps cached of the large
+    fields goes back after each test."""
+    yield
+    gc.collect()
+    torch.cuda.empty_cache()
 
 
 @pytest.fixture(scope="module")

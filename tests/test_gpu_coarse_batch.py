@@ -9,6 +9,8 @@ dispatch and of a 16-field chunk; SAP blocks of 16 sites and of one site.
 Tolerance: a component is a sum of 9d complex products in FP32, whose rounding
 errors add to about sqrt(4 * 9d) 2^-24 <= 3e-6 of it; a smoother step stacks a
 few such products: 1e-5 for both."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -30,6 +32,15 @@ def dd():
     from paper_1307_6101_amd import ddamg
     ddamg.load_library()
     return ddamg
+
+
+@pytest.fixture(autouse=True)
+def _release():
+    """The library allocates beside torch: what torch keeps cached of the large
+    fields goes back after each test."""
+    yield
+    gc.collect()
+    torch.cuda.empty_cache()
 
 
 def _half(a):

@@ -5,6 +5,8 @@ and canonical calls agree bit for bit on either side.
 
 Tolerance: sums of some 100 products per component: 1e-13 in FP64 and 1e-5 in
 FP32; 4 u_16 for FP16 operator storage."""
+import gc
+
 import numpy as np
 import pytest
 import torch
@@ -21,6 +23,15 @@ def dd():
     from paper_1307_6101_amd import ddamg
     ddamg.load_library()
     return ddamg
+
+
+@pytest.fixture(autouse=True)
+def _release():
+    """The library allocates beside torch: what torch keeps cached of the large
+    fields goes back after each test."""
+    yield
+    gc.collect()
+    torch.cuda.empty_cache()
 
 
 # tiles: 1, 4, 64 (the last split), 65, 12 * 6 = 72 of an odd tile grid

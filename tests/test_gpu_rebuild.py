@@ -8,6 +8,7 @@ Tolerance 1e-12 relative, as for the other FP64 setup products: sums of at
 most 3072 products in FP64 (sqrt(3072) 2^-53 = 6e-15) after an
 orthonormalisation whose conditioning for random vectors costs a digit or
 two."""
+import gc
 import time
 
 import numpy as np
@@ -30,6 +31,15 @@ def dd():
     from paper_1307_6101_amd import ddamg
     ddamg.load_library()
     return ddamg
+
+
+@pytest.fixture(autouse=True)
+def _release():
+    """The library allocates beside torch: what torch keeps cached of the large
+    fields goes back after each test."""
+    yield
+    gc.collect()
+    torch.cuda.empty_cache()
 
 
 def _blocks(Dc):
